@@ -16,7 +16,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # the matrix-core kernel families take longest and start first
 SOURCES = ["train_mfma.hip", "decode_mfma.hip", "decode_mfma_frames.hip", "decode_mfma_albedo.hip", "decode_mfma_frames_albedo.hip",
-           "sampler_mfma.hip", "encoder.hip", "train.hip", "train_frames.hip", "decode_f32.hip", "sampler.hip", "fetch.hip", "api.cpp", "material_file.cpp", "precision.cpp",
+           "decode_split.hip", "decode_split_frames.hip", "decode_split_albedo.hip", "decode_split_frames_albedo.hip", "sampler_mfma.hip", "encoder.hip", "train.hip", "train_frames.hip", "decode_f32.hip", "sampler.hip", "fetch.hip", "api.cpp", "material_file.cpp", "precision.cpp",
            "train_api.cpp", "server.cpp"]
 
 # stand-alone measurement programs (probes/), built into _build/ beside the objects

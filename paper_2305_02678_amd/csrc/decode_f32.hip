@@ -1,4 +1,5 @@
-// FP32 decode on the vector ALU: one query per lane, fetch and every decoder layer fused in
+// FP32 decode on the vector ALU (materials the split decode cannot take, and calibration): one
+// query per lane, fetch and every decoder layer fused in
 // one kernel (Eq. neural-brdf; the shading-frame transform T is the material's learned
 // frames when it has them, else the identity).
 //
@@ -8,32 +9,11 @@
 // own column, so no barrier is needed.  Weights are read with wave-uniform (scalar) loads
 // from a per-layer transposed copy [in][out] followed by the bias, so that one input's
 // weights for all outputs are contiguous.
-#include "frames.h"
-#include "latent_fetch.h"
+#include "decode_vec.h"
 
 namespace nam {
 
 constexpr int kF32Threads = 128;
-
-__device__ __forceinline__ float softplus_f32(float q) {
-    // max(q, 0) + log(1 + exp(-|q|)), exact for every q without a threshold
-    return fmaxf(q, 0.0f) + log1pf(expf(-fabsf(q)));
-}
-
-// out[o] = sum_j Wt[j][o] * col[j] + bias[o], j < IN, o < OUT; Wt and bias wave-uniform.
-template <int IN, int OUT>
-__device__ __forceinline__ void dense_from_lds(const float* __restrict__ Wt, const float* col, float* out) {
-    const float* bias = Wt + IN * OUT;
-    #pragma unroll
-    for (int o = 0; o < OUT; ++o) out[o] = bias[o];
-    #pragma unroll 2
-    for (int j = 0; j < IN; ++j) {
-        const float aj = col[j * kF32Threads];
-        const float* wj = Wt + j * OUT;
-        #pragma unroll
-        for (int o = 0; o < OUT; ++o) out[o] = fmaf(wj[o], aj, out[o]);
-    }
-}
 
 // NW: 3-vectors per direction in the network input (1 without frames or with one frame, 2
 // with two frames); nf: the material's frame count (0: T is the identity); NO: decoder
@@ -101,7 +81,7 @@ decode_f32_kernel(PyrArgs p, const float* __restrict__ tex32, const __half* __re
     const float* W = wt;
     {
         float h[H];
-        dense_from_lds<C + 6 * NW, H>(W, col, h);
+        dense_from_lds<C + 6 * NW, H, kF32Threads>(W, col, h);
         float m = 0.0f;
         #pragma unroll
         for (int o = 0; o < H; ++o) { h[o] = fmaxf(h[o], 0.0f); col[o * kF32Threads] = h[o]; m = fmaxf(m, h[o]); }
@@ -111,7 +91,7 @@ decode_f32_kernel(PyrArgs p, const float* __restrict__ tex32, const __half* __re
     #pragma unroll
     for (int k = 1; k < NH; ++k) {
         float h[H];
-        dense_from_lds<H, H>(W, col, h);
+        dense_from_lds<H, H, kF32Threads>(W, col, h);
         float m = 0.0f;
         #pragma unroll
         for (int o = 0; o < H; ++o) { h[o] = fmaxf(h[o], 0.0f); col[o * kF32Threads] = h[o]; m = fmaxf(m, h[o]); }
@@ -120,7 +100,7 @@ decode_f32_kernel(PyrArgs p, const float* __restrict__ tex32, const __half* __re
     }
     // output layer (softplus)
     float qv[NO];
-    dense_from_lds<H, NO>(W, col, qv);
+    dense_from_lds<H, NO, kF32Threads>(W, col, qv);
     if constexpr (CALIB) {
         #pragma unroll
         for (int k = 0; k <= NH; ++k) {

@@ -165,17 +165,16 @@ __device__ __forceinline__ void axis32(float c, float W, int wm, int& x0, int& x
     }
 }
 
-// Bilinear stencil of one level as byte offsets of the 4 texels (C FP16 channels each); weights
+// Bilinear stencil of one level as byte offsets of the 4 texels (2^kShift bytes each); weights
 // scaled by the level weight.
-template <int C, int ADDR>
+template <int kShift, int ADDR>
 __device__ __forceinline__ void level_stencil32(const LevelRowL& row, float u, float v, uint32_t* off, float* w,
                                                 float scale) {
-    constexpr int kShift = C == 16 ? 5 : 4;      // log2 of the texel size in bytes
     int x0, x1, y0, y1;
     float ax, by;
     axis32<ADDR>(u, row.wf, row.wm, x0, x1, ax);
     axis32<ADDR>(v, row.hf, row.hm, y0, y1, by);
-    const uint32_t r0 = row.offb + __umul24((uint32_t)y0, row.pitchb);   // y < 2^15, pitch < 2^20
+    const uint32_t r0 = row.offb + __umul24((uint32_t)y0, row.pitchb);   // y < 2^15, pitch < 2^22
     const uint32_t r1 = row.offb + __umul24((uint32_t)y1, row.pitchb);
     const uint32_t c0 = (uint32_t)x0 << kShift, c1 = (uint32_t)x1 << kShift;
     off[0] = r0 + c0;
@@ -195,7 +194,7 @@ __device__ __forceinline__ void level_stencil32(const LevelRowL& row, float u, f
 // takes the finer level), 4 bilinear taps at full weight (Sec. 4.1).  A non-finite query
 // filters at (0, 0, 0), so every load stays inside the pyramid; its result is replaced by NaN
 // (non-finite) or dropped (past the end of the batch) through the per-query flag.
-template <int C, int ADDR, bool RR>
+template <int kShift, int ADDR, bool RR>
 __device__ __forceinline__ void tap_stencil(int M, const LevelRowL* rows, bool use, float u, float v, float l,
                                             float xi, uint32_t* off, float* w) {
     u = use ? u : 0.0f;
@@ -210,10 +209,10 @@ __device__ __forceinline__ void tap_stencil(int M, const LevelRowL* rows, bool u
     const int l1 = min(l0 + 1, M - 1);
     const float tt = lam - (float)l0;
     if constexpr (RR) {
-        level_stencil32<C, ADDR>(rows[xi < tt ? l1 : l0], u, v, off, w, 1.0f);
+        level_stencil32<kShift, ADDR>(rows[xi < tt ? l1 : l0], u, v, off, w, 1.0f);
     } else {
-        level_stencil32<C, ADDR>(rows[l0], u, v, off, w, 1.0f - tt);
-        level_stencil32<C, ADDR>(rows[l1], u, v, off + 4, w + 4, tt);
+        level_stencil32<kShift, ADDR>(rows[l0], u, v, off, w, 1.0f - tt);
+        level_stencil32<kShift, ADDR>(rows[l1], u, v, off + 4, w + 4, tt);
     }
 }
 
@@ -539,7 +538,7 @@ __global__ void __launch_bounds__(kBlock, 1) decode_mfma_kernel(const MfmaLaunch
         const uint64_t okm = __ballot(okc);
         uint32_t off[NT];
         float w[NT];
-        tap_stencil<C, ADDR, RR>(a.pyr.M, lrows, use, uv.x, uv.y, lod, xi, off, w);
+        tap_stencil<C == 16 ? 5 : 4, ADDR, RR>(a.pyr.M, lrows, use, uv.x, uv.y, lod, xi, off, w);
         float dir[6];
         {
             const float* wi = chunk_elem<3>(a.wi, n, first, lane);

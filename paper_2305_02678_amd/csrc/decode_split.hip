@@ -1,0 +1,230 @@
+// Host side of the split FP32 decode (decode_split.h): the scales and operand blocks of a
+// material, prepared once when it is loaded, and the launch; the kernels of decoders without
+// learned frames and albedo head are instantiated here.
+#include "decode_split.h"
+
+#include <cmath>
+#include <cstring>
+#include <vector>
+
+namespace nam {
+
+hipError_t dispatch_split(const MlpShape& sh, SplitArgs& a, int cu, hipStream_t s) {
+    return dispatch_split_filter<false, false>(sh, a, cu, s);
+}
+
+// Largest |x| as float bits (NaN counts as the largest).
+__global__ void __launch_bounds__(256) absmax_kernel(const uint4* __restrict__ p, int64_t count, unsigned int* __restrict__ out) {
+    unsigned int m = 0;
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x) {
+        const uint4 v = p[i];
+        m = max(max(max(v.x & 0x7fffffffu, v.y & 0x7fffffffu), max(v.z & 0x7fffffffu, v.w & 0x7fffffffu)), m);
+    }
+    for (int o = 32; o > 0; o >>= 1) m = max(m, (unsigned int)__shfl_xor((int)m, o, 64));
+    if ((threadIdx.x & 63) == 0) atomicMax(out, m);
+}
+
+// The largest power of two s with s x <= top (1 for x = 0).
+static double scale_to(double top, double x) {
+    int e = 0;
+    if (!(x > 0.0)) return 1.0;
+    (void)std::frexp(top / x, &e);
+    return std::ldexp(1.0, e - 1);
+}
+
+static bool usable_scale(double s) { return s >= std::ldexp(1.0, -100) && s <= std::ldexp(1.0, 100); }
+
+// The parts of v (a float times a power of two), `stride` bytes apart.
+static void put_parts(uint8_t* dst, size_t stride, int parts, double v) {
+    float rest = (float)v;
+    for (int i = 0; i < parts; ++i) {
+        const _Float16 h = (_Float16)rest;
+        std::memcpy(dst + i * stride, &h, 2);
+        rest -= (float)h;                       // exact
+    }
+}
+
+// Bytes of the A blocks: layer 0 in three parts, the rest as split_parts has it.
+static size_t split_block_offset(const MfmaLayout& lay, int H, int block) {
+    const size_t b0 = std::min(block, lay.RT);
+    return b0 * 3072 + (block - b0) * 1024 * split_parts(H);
+}
+
+hipError_t prepare_decode_split(nam_material* m) {
+    const MlpShape& sh = m->shape;
+    const int C = sh.C, NH = sh.NH, NO = sh.NO, rows_f = 6 * sh.NF;
+    // 32-bit byte offsets into the FP32 texels
+    if (m->texel_count * C * 4 >= (int64_t(1) << 32)) return hipSuccess;
+    for (float p : m->host_params)
+        if (!std::isfinite(p)) return hipSuccess;
+    for (float p : m->host_frames)
+        if (!std::isfinite(p)) return hipSuccess;
+
+    unsigned int* dmax = nullptr;
+    hipError_t e = hipMalloc(&dmax, sizeof(unsigned int));
+    if (e != hipSuccess) return e;
+    unsigned int bits = 0;
+    e = hipMemset(dmax, 0, sizeof(unsigned int));
+    if (e == hipSuccess) {
+        clear_stale_hip_error();
+        absmax_kernel<<<m->ctx->cu_count * 8, 256, 0, nullptr>>>(reinterpret_cast<const uint4*>(m->texels32),
+                                                                 m->texel_count * C / 4, dmax);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipMemcpy(&bits, dmax, sizeof(bits), hipMemcpyDeviceToHost);
+    (void)hipFree(dmax);
+    if (e != hipSuccess) return e;
+    float zmax;
+    std::memcpy(&zmax, &bits, 4);
+    if (!std::isfinite(zmax)) return hipSuccess;
+
+    // Scales.  T: a layer's accumulator holds T times its pre-activation; S: its output's halves
+    // hold S times its activation, S bound <= 2^15.  `err` follows the subnormal step of the low
+    // halves (at most 2^-25 / S per value, independent over a row) to the output.
+    // Directions: |T w| <= sqrt(3) max |w_i|; the same bound without frames, so that an identity
+    // frame changes no bit.
+    const double dirs = 1.75 * kSplitMaxDir;
+    const MfmaLayout lay = mfma_layout(C, sh.H, NH, true, false);
+    const int nB = lay.b_blocks();
+    const size_t a_bytes = split_block_offset(lay, sh.H, lay.a_blocks());
+    std::vector<uint8_t> host(a_bytes + (size_t)nB * 64 + (rows_f ? 1024 + 64 : 0), 0);
+    float* bias = reinterpret_cast<float*>(host.data() + a_bytes);
+    double bound = std::max((double)zmax, dirs);
+    double S = scale_to(32768.0, bound), err = 0.0;
+    if (!usable_scale(S)) return hipSuccess;
+    SplitScales sc{};
+    sc.s0 = (float)S;
+    size_t off = 0;
+    for (int L = 0; L <= NH; ++L) {
+        const int fi = m->dims[L], fo = m->dims[L + 1];
+        const float* W = m->host_params.data() + off;
+        const float* b = W + (size_t)fi * fo;
+        off += (size_t)fi * fo + fo;
+        double wmax = 0.0, next = 0.0, norm = 0.0;
+        for (int r = 0; r < fo; ++r) {
+            double sum = std::fabs((double)b[r]), sq = 0.0;
+            for (int j = 0; j < fi; ++j) {
+                const double w = std::fabs((double)W[(size_t)r * fi + j]);
+                wmax = std::max(wmax, w);
+                sum += w * (L > 0 ? bound : j < C ? (double)zmax : dirs);
+                sq += w * w;
+            }
+            next = std::max(next, sum);
+            norm = std::max(norm, std::sqrt(sq));
+        }
+        err = (err + std::ldexp(1.0, -25) / S) * norm;
+        // every row of the output layer has a scale of its own (RGB does not depend on an albedo head)
+        double T[64];
+        for (int r = 0; r < fo; ++r) {
+            double top = wmax;
+            if (L == NH) {
+                top = 0.0;
+                for (int j = 0; j < fi; ++j) top = std::max(top, std::fabs((double)W[(size_t)r * fi + j]));
+            }
+            const double up = scale_to(1023.0, top);
+            T[r] = up * S;
+            if (!usable_scale(T[r])) return hipSuccess;
+        }
+        const int rts = L < NH ? lay.RT : 1, kss = L == 0 ? 1 : lay.KS;
+        for (int j = 0; j < rts; ++j) {
+            for (int s = 0; s < kss; ++s) {
+                uint8_t* blk = host.data() + split_block_offset(lay, sh.H, lay.a_index(L, j, s));
+                for (int lane = 0; lane < 64; ++lane) {
+                    const int row = 16 * j + lane % 16;
+                    for (int x = 0; x < 8; ++x) {
+                        int in = MfmaLayout::k_source(L, s, lane / 16, x);
+                        if (L > 0 && sh.H == 16 && x >= 4) {
+                            // slots past 16 inputs: the inputs' last bits, weighed by the high halves
+                            in = MfmaLayout::k_source(L, s, lane / 16, x - 4);
+                            if (row < fo && in < fi)
+                                put_parts(blk + lane * 16 + 2 * x, 1024, 1, (double)W[(size_t)row * fi + in] * (T[row] / S));
+                            continue;
+                        }
+                        if (row < fo && in < fi)
+                            put_parts(blk + lane * 16 + 2 * x, 1024, L == 0 ? 3 : split_parts(sh.H),
+                                      (double)W[(size_t)row * fi + in] * (T[row] / S));
+                    }
+                }
+            }
+            float* bb = bias + (size_t)lay.b_index(L, j) * 16;
+            for (int i = 0; i < 16; ++i)
+                if (16 * j + i < fo) bb[i] = (float)((double)b[16 * j + i] * T[16 * j + i]);
+        }
+        if (L < NH) {
+            const double Sn = scale_to(32768.0, next);
+            if (!usable_scale(Sn) || !usable_scale(Sn / T[0])) return hipSuccess;
+            sc.c[L] = (float)(Sn / T[0]);
+            S = Sn;
+            bound = next;
+        } else {
+            for (int r = 0; r < NO; ++r) sc.oinv[r] = (float)(1.0 / T[r]);
+        }
+    }
+    // a quarter of the rounding of an FP32 output near 1
+    if (!(err <= std::ldexp(1.0, -26))) return hipSuccess;
+    if (rows_f) {
+        const float* W = m->host_frames.data();
+        double top = 0.0;
+        for (int i = 0; i < rows_f * C; ++i) top = std::max(top, std::fabs((double)W[i]));
+        const double up = scale_to(1023.0, top), T = up * sc.s0;
+        if (!usable_scale(T)) return hipSuccess;
+        uint8_t* wf = host.data() + a_bytes + (size_t)nB * 64;
+        float* fb = reinterpret_cast<float*>(wf + 1024);
+        for (int lane = 0; lane < 64; ++lane)
+            for (int x = 0; x < 4; ++x) {
+                const int r = lane % 16, ch = 4 * (lane / 16) + x;
+                if (r < rows_f && ch < C) put_parts(wf + lane * 8 + 2 * x, 512, 2, (double)W[r * C + ch] * up);
+            }
+        for (int r = 0; r < rows_f; ++r) fb[r] = (float)((double)W[rows_f * C + r] * T);
+        sc.finv = (float)(1.0 / T);
+    }
+    void* dev = nullptr;
+    if ((e = hipMalloc(&dev, host.size())) != hipSuccess) return e;
+    if ((e = hipMemcpy(dev, host.data(), host.size(), hipMemcpyHostToDevice)) != hipSuccess) {
+        (void)hipFree(dev);
+        return e;
+    }
+    m->split = dev;
+    m->split_bytes = host.size();
+    m->split_scales = sc;
+    return hipSuccess;
+}
+
+hipError_t launch_decode_split(const nam_material* m, int64_t n, const float* uv, const float* lod, const float* xi,
+                               const float* wi, const float* wo, float* rgb, hipStream_t st) {
+    if (n <= 0) return hipSuccess;
+    if (!m->split || n > (int64_t(1) << 30)) return hipErrorInvalidValue;
+    const MfmaLayout lay = mfma_layout(m->shape.C, m->shape.H, m->shape.NH, true, false);
+    const char* base = static_cast<const char*>(m->split);
+    SplitArgs a{};
+    a.pyr = m->pyr();
+    a.tex = m->texels32;
+    a.w = reinterpret_cast<const uint4*>(base);
+    base += split_block_offset(lay, m->shape.H, lay.a_blocks());
+    a.bias = reinterpret_cast<const floatx4*>(base);
+    base += (size_t)lay.b_blocks() * 64;
+    a.wf = reinterpret_cast<const half4*>(base);
+    a.fbias = reinterpret_cast<const floatx4*>(base + 1024);
+    const SplitScales& sc = m->split_scales;
+    a.one = 1.0f;
+    a.s0 = sc.s0;
+    a.finv = sc.finv;
+    for (int k = 0; k < kMaxLayers; ++k) a.c[k] = 0.5f * sc.c[k];
+    std::copy(sc.oinv, sc.oinv + 6, a.oinv);
+    a.n = (int)n;
+    a.nchunks = (int)((n + kChunk - 1) / kChunk);
+    a.nf = m->shape.NF;
+    a.uv = reinterpret_cast<const float2*>(uv);
+    a.lod = lod;
+    a.xi = xi;
+    a.wi = wi;
+    a.wo = wo;
+    a.rgb = rgb;
+    a.wt32 = m->wt32;
+    a.frames32 = m->frames32;
+    const int cu = m->ctx->cu_count;
+    if (m->shape.NF) return m->shape.NO == 6 ? dispatch_split_frames_albedo(m->shape, a, cu, st) : dispatch_split_frames(m->shape, a, cu, st);
+    return m->shape.NO == 6 ? dispatch_split_albedo(m->shape, a, cu, st) : dispatch_split(m->shape, a, cu, st);
+}
+
+}  // namespace nam

@@ -40,6 +40,12 @@ struct MlpShape {
     int in_dim() const { return C + 6 * dir_groups(); }
 };
 
+// Powers of two of the split FP32 decode (decode_split.h): network input, accumulator of layer k
+// to the input of layer k + 1, output accumulator rows to q, frame layer accumulator to its value.
+struct SplitScales {
+    float s0, c[kMaxLayers], oinv[6], finv;
+};
+
 // Looks up the current device's copy of the static region used by nam_loss_backward_noalloc
 // (once per device; *out = NULL if the lookup failed).
 void bind_fixed_scratch(int device, void** out);
@@ -100,6 +106,9 @@ struct nam_material {
     float* fblob = nullptr;                   // device, the FP32 decoder packed for the FP32 matrix cores
                                               // (plain FP32 decodes; decoders the training kernel takes)
     size_t fblob_bytes = 0;
+    void* split = nullptr;                    // device, the FP32 decoder as FP16 halves (decode_split.h);
+    size_t split_bytes = 0;                   // null where its scales do not exist
+    nam::SplitScales split_scales{};
     void* wmfma = nullptr;                    // device, MFMA-packed low-precision decoder
     size_t wmfma_bytes = 0;
     size_t wmfma_bias_offset = 0;             // bytes from wmfma to the bias blocks
@@ -146,7 +155,13 @@ hipError_t launch_popcount(const uint32_t* bitmap, int64_t words, unsigned long 
 // xi: per-query draws for the Russian-roulette level choice, or nullptr for trilinear filtering
 hipError_t launch_decode_f32(const nam_material* m, int64_t n, const float* uv, const float* lod, const float* xi,
                              const float* wi, const float* wo, float* rgb, hipStream_t s);
-// Plain trilinear FP32 decodes on the FP32 matrix cores (the training kernel's forward), for the
+// FP32 decodes on the FP16 matrix cores in split halves: prepare packs the decoder into m->split
+// once and leaves it null where the material's values rule it out (or the texels reach 4 GiB);
+// the launch needs it (n at most 2^30).
+hipError_t prepare_decode_split(nam_material* m);
+hipError_t launch_decode_split(const nam_material* m, int64_t n, const float* uv, const float* lod, const float* xi,
+                               const float* wi, const float* wo, float* rgb, hipStream_t s);
+// Materials without a split decoder: plain trilinear FP32 decodes on the FP32 matrix cores (the training kernel's forward), for the
 // decoders that kernel takes (C in {8, 16}, H in {32, 64}, 2 or 3 hidden layers, 3 or 6
 // outputs, no frames; 32-bit texel offsets): prepare packs the decoder into m->fblob once and
 // leaves it null where unsupported; the launch needs it (n below 2^31).

@@ -123,7 +123,7 @@ __global__ void __launch_bounds__(kBlock, 1) sampler_mfma_kernel(const SamplerMf
         const bool use = query_ok(uv.x, uv.y, lod);
         uint32_t off[NT];
         float w[NT];
-        tap_stencil<C, ADDR, false>(a.pyr.M, sm.rows, use, uv.x, uv.y, lod, 0.0f, off, w);
+        tap_stencil<C == 16 ? 5 : 4, ADDR, false>(a.pyr.M, sm.rows, use, uv.x, uv.y, lod, 0.0f, off, w);
         float wi[3], e3[3] = {0.0f, 0.0f, 0.0f};
         {
             const float* p = chunk_elem<3>(a.wi, n, first, lane);

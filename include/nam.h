@@ -286,9 +286,8 @@ nam_status nam_texel_footprint_stochastic(nam_ctx* ctx, const nam_material* mat,
  * (dims[0] = C + 6 N, T and its conventions as in nam_material_load_framed) and params holds
  * the frame layer first, W_F[6N][C] then b_F[6N], followed by the packed decoder; gradients
  * and Adam moments keep that layout, so the frame layer is trained like every other weight.
- * Training with frames runs on the vector training kernel (its weight gradients on FP32
- * matrix-core tiles) and supports C in {8, 16}, hidden widths 32 or 64, 2 or 3 hidden layers
- * and 3 outputs (NAM_E_UNSUPPORTED otherwise).  n_frames = 0: no
+ * Training with frames supports C in {8, 16}, hidden widths 32 or 64, 2 or 3 hidden layers and
+ * 3 outputs (NAM_E_UNSUPPORTED otherwise).  n_frames = 0: no
  * frames (T the identity, dims[0] = C + 6). */
 typedef struct {
     nam_pyramid_desc pyramid;
@@ -321,11 +320,11 @@ nam_status nam_loss_backward(nam_ctx* ctx, const nam_model_desc* model, const fl
 /* nam_loss_backward for callers that cannot allocate device memory: code under HIP graph
  * capture, tight serving or training loops, and harnesses that forbid hipMalloc.  The same
  * arguments and results as nam_loss_backward, but the call allocates nothing: its level table,
- * the decoder's operand blocks and the per-wave partial gradients and loss sums sit in a static
+ * the decoder's operand blocks and the partial gradients and loss sums sit in a static
  * device region of the library, 32 MiB, one copy per GPU the library runs on, held until the
  * process ends.  The caller still passes the inputs, d_texels, d_params and loss.  The number of
- * workgroups shrinks to what the region holds (each needs 4 (P + 1) floats per wave for a decoder
- * of P parameters), so large decoders may run on fewer CUs than nam_loss_backward uses; the
+ * workgroups shrinks to what the region holds (each needs 4 (P + 1) floats for a decoder of P
+ * parameters), so large decoders may run on fewer CUs than nam_loss_backward uses; the
  * gradients are those of nam_loss_backward to rounding (the per-slice partial sums are grouped
  * differently).  Every call on one GPU shares the region: calls that overlap on one GPU (two
  * streams, two host threads, two contexts) race and give undefined results; calls in one stream

@@ -187,16 +187,12 @@ nam_status run(nam_ctx* ctx, const nam_model_desc* md, int mode, const float* te
     const int np = m.np();
     // the matrix-core kernels address texel channels with 32-bit offsets
     const bool mfma = train_mfma_supported(m.shape) && m.texels * md->pyramid.channels < (int64_t(1) << 31);
-    int grid, slices;
+    int grid, pairs = 0, slices;
     if (mfma) {
-        // one workgroup of 4 waves per CU (the decoder's blocks fill most of the LDS); one
-        // partial slice per wave, 16 samples per tile
-        const int64_t tiles = (n + 15) / 16;
-        int64_t waves = (int64_t)ctx->cu_count * 4;
-        if (waves > tiles) waves = tiles;
-        grid = (int)((waves + 3) / 4);
-        if (grid < 1) grid = 1;
-        slices = grid * 4;
+        // one workgroup per CU (the decoder's blocks fill most of the LDS), one partial slice per pair
+        // of waves
+        train_mfma_grid(n, ctx->cu_count, mode != kModeForward, &grid, &pairs);
+        slices = grid * (pairs > 0 ? pairs : 1);
     } else {
         const int64_t nchunks = (n + 63) / 64;
         grid = ctx->cu_count * fwdbwd_blocks_per_cu(m.shape, mode);
@@ -216,14 +212,14 @@ nam_status run(nam_ctx* ctx, const nam_model_desc* md, int mode, const float* te
         const size_t fixed_bytes = kRowsBytes + wt_bytes + 256 * 2;
         const size_t per_slice = (size_t)np * 4 + 4;
         int64_t max_slices = fws->bytes > fixed_bytes ? (int64_t)((fws->bytes - fixed_bytes) / per_slice) : 0;
-        if (mfma) max_slices -= max_slices % 4;
-        if (max_slices < (mfma ? 4 : 1))
+        if (mfma) max_slices -= max_slices % pairs;
+        if (max_slices < (mfma ? pairs : 1))
             return set_error(NAM_E_UNSUPPORTED,
                              "the decoder's gradients do not fit the library's static scratch (" +
                                  std::to_string(fws->bytes >> 20) + " MiB; " + std::to_string(np) + " parameters)");
         if (slices > max_slices) {
             slices = (int)max_slices;
-            grid = mfma ? slices / 4 : slices;
+            grid = mfma ? slices / pairs : slices;
         }
         LevelRow* rows = reinterpret_cast<LevelRow*>(fws->base);
         NAM_HIP(launch_level_rows(md->pyramid.width, md->pyramid.height, md->pyramid.levels, rows, st));
@@ -289,6 +285,7 @@ nam_status run(nam_ctx* ctx, const nam_model_desc* md, int mode, const float* te
     }
     a.blob = wt;
     a.NO = m.shape.NO;
+    a.pairs = pairs;
     if (mfma) NAM_HIP(launch_train_mfma(m.shape, mode != kModeForward, dec, wt, a, grid, st));
     else NAM_HIP(launch_fwdbwd(m.shape, mode, a, grid, st));
     if (det_acc) {

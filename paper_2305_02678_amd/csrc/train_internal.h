@@ -41,7 +41,8 @@ struct TrainArgs {
     // matrix-core kernels: the decoder's packed operand blocks and the number of outputs
     const float* blob;
     int NO;
-    // learned shading frames (vector kernel): W_F[6 NF][C] then b_F[6 NF]; params is then the
+    int pairs;                    // wave pairs per workgroup that take tiles
+    // learned shading frames: W_F[6 NF][C] then b_F[6 NF]; params is then the
     // decoder that follows them, and np counts both
     const float* fparams;
 };
@@ -78,12 +79,13 @@ hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);
 hipError_t launch_fill_f32(float* p, int64_t count, float v, hipStream_t s);
 // The level table of a pyramid computed on the device (no host copy): rows[l] for l < levels.
 hipError_t launch_level_rows(int width, int height, int levels, LevelRow* rows, hipStream_t s);
-// Matrix-core training path (decoders C in {8, 16}, H in {32, 64}, 2 or 3 hidden layers, no
-// frames): packs the decoder into blob (train_mfma_blob_floats(sh) floats), then runs the
-// forward (train = false) or the forward-backward kernel, grid workgroups of 4 waves; partial
-// and loss_partial hold one slice per wave.
+// Matrix-core training path (train_mfma.h): packs the decoder (and a.fparams) into blob
+// (train_mfma_blob_floats(sh) floats), then runs the forward (train = false) or the forward-backward
+// kernel on `grid` workgroups; partial and loss_partial hold one slice per wave pair, grid x pairs as
+// train_mfma_grid gives them (a.pairs = *pairs; a small batch spreads over the CUs first).
 bool train_mfma_supported(const MlpShape& sh);
 int train_mfma_blob_floats(const MlpShape& sh);
+void train_mfma_grid(int64_t n, int cu_count, bool train, int* grid, int* pairs);
 hipError_t launch_train_mfma(const MlpShape& sh, bool train, const float* params, float* blob, const TrainArgs& a,
                              int grid, hipStream_t st);
 // Deterministic scatter of dz into the texels: fixed-point 64-bit integer atomics (exactly

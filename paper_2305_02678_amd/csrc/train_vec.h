@@ -1,5 +1,6 @@
 // The FP32 vector-ALU training kernel (one sample per lane; see train.hip), shared by the
-// plain and the learned-shading-frame instantiations.
+// plain and the learned-shading-frame instantiations: the shapes and sizes the matrix-core kernel
+// (train_mfma.h) does not take (64-wide decoders of four hidden layers, pyramids of 2^31 values).
 #pragma once
 
 #include "frames.h"

@@ -293,8 +293,8 @@ nam_status run(nam_ctx* ctx, const nam_model_desc* md, int mode, const float* te
                                    det_acc, d_texels, st));
         NAM_HIP(launch_det_finish(m.texels * md->pyramid.channels, det_acc, a.dz_absmax, a.n, d_texels, st));
     }
-    if (mode != kModeForward) NAM_HIP(launch_reduce_partials(partial, slices, np, d_params, st));
-    if (mode == kModeLoss && loss) NAM_HIP(launch_reduce_loss(loss_part, slices, a.inv_count, loss, st));
+    if (mode != kModeForward)
+        NAM_HIP(launch_reduce(partial, slices, np, d_params, loss_part, a.inv_count, mode == kModeLoss ? loss : nullptr, st));
     return NAM_OK;
 }
 
@@ -426,7 +426,7 @@ nam_status nam_train_step(nam_ctx* ctx, const nam_model_desc* md, float* texels,
     float* g_tex = static_cast<float*>(ctx->grad_ws);
     float* g_par = reinterpret_cast<float*>(static_cast<char*>(ctx->grad_ws) + gtex_bytes);
     hipStream_t st = (hipStream_t)stream;
-    NAM_HIP(hipMemsetAsync(g_tex, 0, (size_t)tex_count * 4, st));
+    NAM_HIP(launch_zero(g_tex, (size_t)tex_count * 4, st));         // C >= 8 floats per texel: 16-byte words
     s = run(ctx, md, kModeLoss, texels, params, n, uv, lod, wi, wo, target, nullptr, nullptr, g_tex, g_par, loss, st);
     if (s != NAM_OK) return s;
     NAM_HIP(launch_adam(np, params, m_params, v_params, g_par, cfg->lr, cfg->beta1, cfg->beta2, cfg->eps, c1, c2, st));
@@ -491,7 +491,7 @@ static nam_status encoder_run(nam_ctx* ctx, const nam_mlp_desc* enc, const float
     if (s != NAM_OK) return s;
     a.partial = static_cast<float*>(ctx->train_ws);
     NAM_HIP(launch_encoder(A, C, HE, NHE, 2, a, grid, st));
-    NAM_HIP(launch_reduce_partials(a.partial, grid, np, d_eparams, st));
+    NAM_HIP(launch_reduce(a.partial, grid, np, d_eparams, nullptr, 0.0f, nullptr, st));
     return NAM_OK;
 }
 

@@ -34,6 +34,7 @@ struct SamplerMfmaArgs {
     int n;
     int nchunks;
     int groups;               // XCD groups: min(8, grid); the grid is a multiple of it
+    int wpb;                  // waves of a workgroup that take chunks
     int mode;                 // SamplerMode
     const float2* uv;
     const float* lod;
@@ -106,10 +107,10 @@ __global__ void __launch_bounds__(kBlock, 1) sampler_mfma_kernel(const SamplerMf
 
     const int X = a.groups;
     const int grp = (int)blockIdx.x % X;
-    const int stride = ((int)gridDim.x / X) * kWaves;
-    int c = (int)((int64_t)a.nchunks * grp / X) + ((int)blockIdx.x / X) * kWaves + wave;
+    const int stride = ((int)gridDim.x / X) * a.wpb;
+    int c = (int)((int64_t)a.nchunks * grp / X) + ((int)blockIdx.x / X) * a.wpb + wave;
     const int c_end = (int)((int64_t)a.nchunks * (grp + 1) / X);
-    if (c >= c_end) return;
+    if (wave >= a.wpb || c >= c_end) return;
     const int n = a.n;
     const int mode = a.mode;
     uint8_t* const reg = sm.wreg[wave];
@@ -249,11 +250,12 @@ static hipError_t launch_sampler_mfma_shape(SamplerMfmaArgs& a, int cu_count, hi
             b = 1;
         return b;
     }();
-    // the persistent grid, no larger than a chunk per wave, a multiple of the XCD groups
-    int grid = std::min(cu_count * blocks_per_cu, (a.nchunks + kWaves - 1) / kWaves);
+    // the persistent grid, a multiple of the XCD groups; few chunks spread over it (split_grid)
+    int grid = std::min(cu_count * blocks_per_cu, a.nchunks);
     if (grid >= 8) grid -= grid % 8;
     grid = std::max(grid, 1);
     a.groups = std::min(grid, 8);
+    a.wpb = std::min(kWaves, (a.nchunks + grid - 1) / grid);
     clear_stale_hip_error();
     sampler_mfma_kernel<C, H, NH, ADDR><<<grid, kBlock, 0, s>>>(a);
     return hipGetLastError();

@@ -131,18 +131,27 @@ struct nam_server {
     int64_t peak_requests_on_device = 0;          // distinct requests with tiles on the device at once
     int64_t peak_launches_on_device = 0;          // launches on the device at once (streams busy)
 
+    // Submissions enter through an inbox with a lock of its own, so that a submitting thread does not
+    // wait for the worker, which holds `mu` while it launches and queries events; whoever holds `mu`
+    // takes them over (drain).  Lock order: mu, then in_mu.
+    std::mutex in_mu;
+    std::condition_variable in_cv;                // wakes the worker
+    std::vector<Request*> inbox;
+    uint64_t next_ticket = 1;
+    bool wake = false;
+    std::atomic<int> material_count{0};
+
     std::mutex mu;
-    std::condition_variable cv;                   // wakes the worker
     std::condition_variable done_cv;              // wakes waiters
     std::multimap<Clock::time_point, Request*> arrivals;   // not yet arrived (replayed)
     std::deque<Request*> pending;                 // arrived, not fully launched, arrival order
-    std::map<uint64_t, Request*> requests;        // every live request
+    std::map<uint64_t, Request*> requests;        // every request since the last reset
+    int64_t failed = 0;                           // those in state 3
     std::vector<Tile> inflight;
-    uint64_t next_ticket = 1;
     bool stop = false;
     nam_status fatal = NAM_OK;
 
-    // statistics since the last reset; replayed arrival times count from `epoch`
+    // statistics since the last reset; replayed arrival times count from `epoch` (written under both locks)
     Clock::time_point epoch;
     std::vector<double> latencies;
     int64_t done_queries = 0;
@@ -153,6 +162,12 @@ struct nam_server {
 };
 
 namespace {
+
+void fail_request(nam_server* s, Request* r) {
+    if (r->state != 3) s->failed += 1;
+    r->state = 3;
+    r->error = NAM_E_HIP;
+}
 
 // After a launch: how many distinct requests and launches are on the device now.
 void note_on_device(nam_server* s) {
@@ -201,8 +216,7 @@ bool launch_tile(nam_server* s, Request* r, int si, int64_t cnt, Tile* t) {
     if (e == hipSuccess) e = hipEventRecord(t->done, st);
     if (e != hipSuccess) {
         if (r->host_io) s->arena->release(t->arena_off, bytes);
-        r->state = 3;
-        r->error = NAM_E_HIP;
+        fail_request(s, r);
         return false;
     }
     s->reserved += bytes;
@@ -215,12 +229,14 @@ bool launch_tile(nam_server* s, Request* r, int si, int64_t cnt, Tile* t) {
     return true;
 }
 
-// Tiles from the front of the pending queue, in arrival order, whose buffers are on the device
-// and whose materials share the front request's matrix-core kernel, as many as the budget and
-// max_group allow, launched as one grouped kernel on stream si.  Returns the number of tiles
-// launched (0: the first does not fit the budget).
+// Tiles of the front of the pending queue and, in arrival order, of the next kLookAhead requests
+// whose buffers are on the device and whose materials share its matrix-core kernel, as many as the
+// budget and max_group allow, launched as one grouped kernel on stream si.  Requests of other kernels
+// in between stay in line: each launch starts with the oldest.  Returns the number of tiles launched
+// (0: the first does not fit the budget).
 int launch_group(nam_server* s, int si) {
     constexpr int kG = 8;
+    constexpr size_t kLookAhead = 32;
     const nam_material* m0 = s->materials[s->pending.front()->material];
     const nam_material* mats[kG];
     int64_t ns[kG];
@@ -230,11 +246,11 @@ int launch_group(nam_server* s, int si) {
     int count = 0;
     size_t total = 0;
     const int limit = std::min(kG, s->max_group);
-    for (size_t k = 0; k < s->pending.size() && count < limit; ++k) {
+    for (size_t k = 0; k < s->pending.size() && k < kLookAhead && count < limit; ++k) {
         Request* r = s->pending[k];
         if (r->state >= 2 || r->next >= r->n) continue;
         const nam_material* m = s->materials[r->material];
-        if (r->host_io || !nam::mfma_same_kernel(m0, m)) break;
+        if (r->host_io || !nam::mfma_same_kernel(m0, m)) continue;
         int64_t next = r->next;
         for (int j = 0; j < count; ++j)
             if (tiles[j].r == r) next = std::max(next, tiles[j].off + tiles[j].cnt);
@@ -272,8 +288,7 @@ int launch_group(nam_server* s, int si) {
     if (e == hipSuccess) e = hipEventRecord(s->events[si], st);
     if (e != hipSuccess) {
         for (int j = 0; j < count; ++j) {
-            tiles[j].r->state = 3;
-            tiles[j].r->error = NAM_E_HIP;
+            fail_request(s, tiles[j].r);
         }
         return -1;
     }
@@ -302,29 +317,58 @@ void finish_request(nam_server* s, Request* r, Clock::time_point now) {
     s->have_first = true;
 }
 
+// Takes the inbox over (mu held): the requests become known, those without queries are done, the
+// others wait for their arrival time.
+void drain(nam_server* s) {
+    std::vector<Request*> got;
+    {
+        std::lock_guard<std::mutex> g(s->in_mu);
+        got.swap(s->inbox);
+    }
+    for (Request* r : got) {
+        s->requests[r->ticket] = r;
+        if (r->n == 0) finish_request(s, r, r->arrival);
+        else s->arrivals.emplace(r->arrival, r);
+    }
+}
+
+void wake_worker(nam_server* s) {
+    {
+        std::lock_guard<std::mutex> g(s->in_mu);
+        s->wake = true;
+    }
+    s->in_cv.notify_one();
+}
+
 void worker_loop(nam_server* s) {
     (void)hipSetDevice(s->ctx->device);
     std::unique_lock<std::mutex> lk(s->mu);
     while (true) {
+        drain(s);
         const Clock::time_point now = Clock::now();
         // arrivals whose time has come
         while (!s->arrivals.empty() && s->arrivals.begin()->first <= now) {
             s->pending.push_back(s->arrivals.begin()->second);
             s->arrivals.erase(s->arrivals.begin());
         }
-        // retire completed tiles
+        // retire completed tiles (the tiles of a launch share its stream's event: one query each)
         bool progressed = false;
+        hipError_t state[16];
+        bool asked[16] = {};
         for (size_t i = 0; i < s->inflight.size();) {
             Tile& t = s->inflight[i];
-            const hipError_t q = hipEventQuery(t.done);
+            if (!asked[t.stream]) {
+                state[t.stream] = hipEventQuery(t.done);
+                asked[t.stream] = true;
+            }
+            const hipError_t q = state[t.stream];
             if (q == hipErrorNotReady) {
                 ++i;
                 continue;
             }
             Request* r = t.r;
             if (q != hipSuccess) {
-                r->state = 3;
-                r->error = NAM_E_HIP;
+                fail_request(s, r);
             }
             if (t.staged) s->arena->release(t.arena_off, t.bytes);
             s->reserved -= t.bytes;
@@ -377,12 +421,16 @@ void worker_loop(nam_server* s) {
             // short poll interval for the events in flight
             auto until = Clock::now() + std::chrono::microseconds(s->inflight.empty() ? 2000 : 20);
             if (!s->arrivals.empty()) until = std::min(until, s->arrivals.begin()->first);
-            if (s->inflight.empty()) s->cv.wait_until(lk, until);
-            else {
-                lk.unlock();
+            const bool idle = s->inflight.empty();
+            lk.unlock();
+            if (idle) {
+                std::unique_lock<std::mutex> in(s->in_mu);
+                s->in_cv.wait_until(in, until, [s] { return s->wake || !s->inbox.empty(); });
+                s->wake = false;
+            } else {
                 std::this_thread::yield();
-                lk.lock();
             }
+            lk.lock();
         }
     }
 }
@@ -393,12 +441,10 @@ nam_status submit(nam_server* s, int material_id, int64_t n, const float* uv, co
     if (n < 0) return nam::set_error(NAM_E_INVALID_ARG, "n must be >= 0");
     if (n > 0 && (!uv || !lod || !wi || !wo || !rgb)) return nam::set_error(NAM_E_INVALID_ARG, "query pointer is NULL");
     if (!(arrival_s == arrival_s)) return nam::set_error(NAM_E_INVALID_ARG, "arrival time is NaN");
-    std::lock_guard<std::mutex> g(s->mu);
-    if (material_id < 0 || material_id >= (int)s->materials.size())
+    if (material_id < 0 || material_id >= s->material_count.load(std::memory_order_acquire))
         return nam::set_error(NAM_E_INVALID_ARG, "unknown material id");
     Request* r = new (std::nothrow) Request();
     if (!r) return nam::set_error(NAM_E_OOM, "host allocation failed");
-    r->ticket = s->next_ticket++;
     r->material = material_id;
     r->n = n;
     r->uv = uv;
@@ -407,17 +453,19 @@ nam_status submit(nam_server* s, int material_id, int64_t n, const float* uv, co
     r->wo = wo;
     r->rgb = rgb;
     r->host_io = host_io != 0;
-    const Clock::time_point now = Clock::now();
-    r->arrival = arrival_s < 0 ? now
-                               : s->epoch + std::chrono::duration_cast<Clock::duration>(std::chrono::duration<double>(arrival_s));
-    s->requests[r->ticket] = r;
-    *ticket = r->ticket;
-    if (n == 0) {
-        finish_request(s, r, r->arrival);
-        return NAM_OK;
+    try {
+        std::lock_guard<std::mutex> g(s->in_mu);
+        s->inbox.push_back(r);
+        r->ticket = s->next_ticket++;
+        const Clock::time_point now = Clock::now();
+        r->arrival = arrival_s < 0 ? now
+                                   : s->epoch + std::chrono::duration_cast<Clock::duration>(std::chrono::duration<double>(arrival_s));
+        *ticket = r->ticket;
+    } catch (const std::bad_alloc&) {
+        delete r;
+        return nam::set_error(NAM_E_OOM, "host allocation failed");
     }
-    s->arrivals.emplace(r->arrival, r);     // released to the worker in arrival order
-    s->cv.notify_one();
+    s->in_cv.notify_one();
     return NAM_OK;
 }
 
@@ -477,6 +525,7 @@ nam_status nam_server_add_material(nam_server* s, nam_material* m, int* material
     std::lock_guard<std::mutex> g(s->mu);
     m->server_refs++;
     s->materials.push_back(m);
+    s->material_count.store((int)s->materials.size(), std::memory_order_release);
     *material_id = (int)s->materials.size() - 1;
     return NAM_OK;
 }
@@ -490,6 +539,7 @@ nam_status nam_server_submit(nam_server* s, int material_id, int64_t n, const fl
 nam_status nam_server_poll(nam_server* s, uint64_t ticket, int* done, double* latency_s) {
     if (!s || !done) return set_error(NAM_E_INVALID_ARG, "NULL argument");
     std::lock_guard<std::mutex> g(s->mu);
+    drain(s);
     auto it = s->requests.find(ticket);
     if (it == s->requests.end()) return set_error(NAM_E_INVALID_ARG, "unknown ticket");
     Request* r = it->second;
@@ -503,6 +553,7 @@ nam_status nam_server_poll(nam_server* s, uint64_t ticket, int* done, double* la
 nam_status nam_server_cancel(nam_server* s, uint64_t ticket) {
     if (!s) return set_error(NAM_E_INVALID_ARG, "NULL argument");
     std::lock_guard<std::mutex> g(s->mu);
+    drain(s);
     auto it = s->requests.find(ticket);
     if (it == s->requests.end()) return set_error(NAM_E_INVALID_ARG, "unknown ticket");
     Request* r = it->second;
@@ -518,19 +569,19 @@ nam_status nam_server_cancel(nam_server* s, uint64_t ticket) {
 nam_status nam_server_wait_all(nam_server* s) {
     if (!s) return set_error(NAM_E_INVALID_ARG, "NULL argument");
     std::unique_lock<std::mutex> lk(s->mu);
-    s->cv.notify_one();
+    wake_worker(s);
     s->done_cv.wait(lk, [s] {
+        drain(s);
         if (!s->arrivals.empty() || !s->pending.empty() || !s->inflight.empty()) return false;
         return true;
     });
-    for (auto& kv : s->requests)
-        if (kv.second->state == 3) return set_error(NAM_E_HIP, "a request failed on the device");
-    return NAM_OK;
+    return s->failed > 0 ? set_error(NAM_E_HIP, "a request failed on the device") : NAM_OK;
 }
 
 nam_status nam_server_stats(nam_server* s, nam_server_stats_t* out) {
     if (!s || !out) return set_error(NAM_E_INVALID_ARG, "NULL argument");
     std::lock_guard<std::mutex> g(s->mu);
+    drain(s);
     std::memset(out, 0, sizeof(*out));
     std::vector<double> l = s->latencies;
     out->completed = (int64_t)l.size();
@@ -564,8 +615,12 @@ nam_status nam_server_stats(nam_server* s, nam_server_stats_t* out) {
 nam_status nam_server_reset_stats(nam_server* s) {
     if (!s) return set_error(NAM_E_INVALID_ARG, "NULL argument");
     std::lock_guard<std::mutex> g(s->mu);
+    drain(s);
     s->latencies.clear();
-    s->epoch = Clock::now();
+    {
+        std::lock_guard<std::mutex> in(s->in_mu);
+        s->epoch = Clock::now();
+    }
     s->done_queries = 0;
     s->have_first = false;
     s->peak_reserved = s->reserved;
@@ -575,6 +630,7 @@ nam_status nam_server_reset_stats(nam_server* s) {
     s->peak_launches_on_device = 0;
     for (auto it = s->requests.begin(); it != s->requests.end();) {
         if (it->second->state >= 2) {
+            if (it->second->state == 3) s->failed -= 1;
             delete it->second;
             it = s->requests.erase(it);
         } else {
@@ -597,9 +653,10 @@ nam_status nam_server_destroy(nam_server* s) {
     {
         std::lock_guard<std::mutex> g(s->mu);
         s->stop = true;
-        s->cv.notify_one();
     }
+    wake_worker(s);
     s->worker.join();
+    drain(s);                                     // submitted during the destruction: never run
     (void)hipSetDevice(s->ctx->device);
     for (auto st : s->streams) (void)hipStreamSynchronize(st);
     for (auto st : s->streams) (void)hipStreamDestroy(st);

@@ -57,6 +57,7 @@ class AdamCfg(ctypes.Structure):
 
 
 _lib = None
+_torch = None          # set with _lib: the per-call paths below import and look up nothing
 
 
 def header_functions() -> List[str]:
@@ -68,10 +69,11 @@ def header_functions() -> List[str]:
 def lib(build_if_missing: bool = False):
     """Load libnam.so once.  torch is imported first so that the library binds to the HIP
     runtime torch already loaded (one runtime per process)."""
-    global _lib
+    global _lib, _torch
     if _lib is not None:
         return _lib
-    import torch  # noqa: F401  (HIP runtime first)
+    import torch  # (HIP runtime first)
+    _torch = torch
     if not os.path.exists(LIB_PATH):
         if not build_if_missing:
             raise RuntimeError(f"libnam is not built ({LIB_PATH} missing); run python -m paper_2305_02678_amd.build")
@@ -145,22 +147,25 @@ def check(status: int):
 
 
 def _stream(stream=None):
-    import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    """The hipStream_t of a torch stream, or of the current one."""
+    if stream is not None:
+        return stream.cuda_stream
+    raw = _torch._C
+    return raw._cuda_getCurrentRawStream(raw._cuda_getDevice())
 
 
 def _dev(t, shape_tail, name):
-    import torch
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+    """Address of a contiguous float32 CUDA tensor [n, *shape_tail]."""
+    if (isinstance(t, _torch.Tensor) and t.is_cuda and t.dtype is _torch.float32 and t.is_contiguous()
+            and t.shape[1:] == shape_tail):
+        return t.data_ptr()
+    if not isinstance(t, _torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a CUDA tensor")
-    if t.dtype != torch.float32:
+    if t.dtype != _torch.float32:
         raise TypeError(f"{name} must be float32")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if tuple(t.shape[1:]) != tuple(shape_tail):
-        raise ValueError(f"{name} must have shape [n, {', '.join(map(str, shape_tail))}]")
-    return ctypes.c_void_p(t.data_ptr())
+    raise ValueError(f"{name} must have shape [n, {', '.join(map(str, shape_tail))}]")
 
 
 def pyramid_bytes(width, height, channels, levels, texel_type=F16, address=WRAP) -> int:
@@ -354,11 +359,10 @@ def decode(mat: Material, uv, lod, wi, wo, out=None, stream=None, xi=None):
     """nam_decode; with `xi` (one draw per query) nam_decode_stochastic, the level chosen by
     Russian roulette.  out [n][3], or [n][6] (RGB, then albedo) for a decoder with the albedo
     head."""
-    import torch
     n = lod.shape[0]
     ko = mat.dims[-1]
     if out is None:
-        out = torch.empty((n, ko), dtype=torch.float32, device=lod.device)
+        out = _torch.empty((n, ko), dtype=_torch.float32, device=lod.device)
     if xi is None:
         check(lib().nam_decode(mat.ctx.handle, mat.handle, n, _dev(uv, (2,), "uv"), _dev(lod, (), "lod"),
                                _dev(wi, (3,), "wi"), _dev(wo, (3,), "wo"), _dev(out, (ko,), "rgb"), _stream(stream)))
@@ -492,7 +496,7 @@ class Model:
                  _dev(params, (), "params"), n, _dev(uv, (2,), "uv"), _dev(lod, (), "lod"), _dev(wi, (3,), "wi"),
                  _dev(wo, (3,), "wo"), _dev(target, (self.dims[-1],), "target"),
                  _dev(d_texels, (self.channels,), "d_texels"), _dev(d_params, (), "d_params"),
-                 ctypes.c_void_p(loss.data_ptr()), _stream(stream)))
+                 loss.data_ptr(), _stream(stream)))
         return loss, d_texels, d_params
 
 
@@ -508,7 +512,7 @@ class Model:
         check(lib().nam_loss_backward_codes(self.ctx.handle, ctypes.byref(self.desc), _dev(params, (), "params"), n,
                                             _dev(z, (self.channels,), "z"), _dev(wi, (3,), "wi"), _dev(wo, (3,), "wo"),
                                             _dev(target, (self.dims[-1],), "target"), _dev(dz, (self.channels,), "dz"),
-                                            _dev(d_params, (), "d_params"), ctypes.c_void_p(loss.data_ptr()),
+                                            _dev(d_params, (), "d_params"), loss.data_ptr(),
                                             _stream(stream)))
         return loss, dz, d_params
 
@@ -596,7 +600,7 @@ class Trainer:
                                    _dev(self.m_par, (), "m_params"), _dev(self.v_par, (), "v_params"),
                                    lod.shape[0], _dev(uv, (2,), "uv"), _dev(lod, (), "lod"), _dev(wi, (3,), "wi"),
                                    _dev(wo, (3,), "wo"), _dev(target, (md.dims[-1],), "target"), ctypes.byref(cfg),
-                                   ctypes.c_void_p(self.loss.data_ptr()), _stream(stream)))
+                                   self.loss.data_ptr(), _stream(stream)))
         return self.loss
 
 
@@ -637,6 +641,9 @@ def neural_material(texels, params, uv, lod, wi, wo, model: Model):
 # serving
 
 
+_ONE, _PAIR, _TRIPLE = (), (2,), (3,)
+
+
 class Server:
     """Continuous-batching request loop over resident materials (see nam_server_* in nam.h)."""
 
@@ -660,16 +667,15 @@ class Server:
         host = not rgb.is_cuda
         n = lod.shape[0]
         ko = self._materials[material_id].dims[-1] if 0 <= material_id < len(self._materials) else 3
-        for t, tail, name in ((uv, (2,), "uv"), (lod, (), "lod"), (wi, (3,), "wi"), (wo, (3,), "wo"),
+        for t, tail, name in ((uv, _PAIR, "uv"), (lod, _ONE, "lod"), (wi, _TRIPLE, "wi"), (wo, _TRIPLE, "wo"),
                               (rgb, (ko,), "rgb")):
-            if t.is_cuda == host or not t.is_contiguous() or tuple(t.shape[1:]) != tail:
+            if t.is_cuda == host or not t.is_contiguous() or t.shape[1:] != tail:
                 raise ValueError(f"{name}: all buffers on one side (host or device), contiguous, [n{', ' if tail else ''}"
                                  f"{', '.join(map(str, tail))}]")
         tk = ctypes.c_uint64(0)
-        check(lib().nam_server_submit(self.handle, material_id, n, ctypes.c_void_p(uv.data_ptr()),
-                                      ctypes.c_void_p(lod.data_ptr()), ctypes.c_void_p(wi.data_ptr()),
-                                      ctypes.c_void_p(wo.data_ptr()), ctypes.c_void_p(rgb.data_ptr()), int(host),
-                                      -1.0 if arrival_s is None else float(arrival_s), ctypes.byref(tk)))
+        check(_lib.nam_server_submit(self.handle, material_id, n, uv.data_ptr(), lod.data_ptr(), wi.data_ptr(),
+                                     wo.data_ptr(), rgb.data_ptr(), int(host),
+                                     -1.0 if arrival_s is None else float(arrival_s), ctypes.byref(tk)))
         self._keep[tk.value] = (uv, lod, wi, wo, rgb)
         return tk.value
 

@@ -286,6 +286,7 @@ nam_status run(nam_ctx* ctx, const nam_model_desc* md, int mode, const float* te
     a.blob = wt;
     a.NO = m.shape.NO;
     a.pairs = pairs;
+    a.one = 1.0f;
     if (mfma) NAM_HIP(launch_train_mfma(m.shape, mode != kModeForward, dec, wt, a, grid, st));
     else NAM_HIP(launch_fwdbwd(m.shape, mode, a, grid, st));
     if (det_acc) {

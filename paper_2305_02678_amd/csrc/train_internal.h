@@ -42,6 +42,7 @@ struct TrainArgs {
     const float* blob;
     int NO;
     int pairs;                    // wave pairs per workgroup that take tiles
+    float one;                    // 1.0f (split_pair)
     // learned shading frames: W_F[6 NF][C] then b_F[6 NF]; params is then the
     // decoder that follows them, and np counts both
     const float* fparams;

@@ -1,39 +1,54 @@
-// Differentiation of the decode on the gfx950 matrix cores (FP32 v_mfma_f32_16x16x4_f32):
+// Differentiation of the decode on the gfx950 matrix cores:
 // training by backpropagation into the decoder, the learned shading frames and directly into the
 // latent texels (Sec. 5 and the direct optimisation of Sec. 2 "Obtaining latent textures").
 //
 // Work decomposition.  One workgroup of 8 waves per CU, two per SIMD: waves p and p + 4 (on the
 // same SIMD) form a pair that walks its own 16-sample tiles.  The front wave fetches a tile, runs
-// the forward pass and takes the deltas down through the layers, all in registers, and scatters the
-// code's gradient into the texels; the back wave contracts the weight gradients.  Each layer's
-// (deltas, inputs) pass from front to back through two 8 KiB slots of LDS per pair, so the back
-// wave's matrix-core chains fill the front wave's latencies (taps, texels, atomics, softplus), and
-// neither wave holds the other's registers (one wave doing both needs 428 + 72, a single wave per
-// SIMD).  The decoder's operand blocks (below) sit in LDS, shared by the workgroup.
+// the forward pass and takes the deltas down through the layers, all in registers; the back wave
+// contracts the weight gradients and, between the layers of the next tile, scatters the code's gradient
+// into the texels.  Each layer's (deltas, inputs) pass from front to back through two 8 KiB slots of
+// LDS per pair, so the back wave's matrix-core chains and atomics fill the front wave's latencies
+// (taps, texels, softplus), and neither wave holds the other's registers.  The decoder's operand blocks sit in LDS, shared by the
+// workgroup.
 //
-// Lane (g, s) = (lane / 16, lane % 16) works on sample s of the tile.  A layer is Y = W X with the
-// weights as the A operand (16 output rows per row tile) and one sample per column; its accumulator
-// leaves lane (g, s) holding row slots 4g..4g+3 of each row tile.  The next layer takes K steps (t, r)
-// = {slots 16t + 4g + r : g = 0..3}, so the accumulator registers [t][r] are exactly its B operands:
-// the weights' K order is permuted when they are packed, and no activation moves between lanes.
-// Slot 4g + r of a row tile holds neuron 4g + r or, in natural order, neuron 4r + g: then the K steps
-// run over the neurons in ascending order, and as the instruction is a chain of four FMAs in
-// ascending k, a layer's sums are bit for bit those of the vector kernel (train_vec.h), whose shapes
-// (learned frames, width 16, 1 or 4 hidden layers) it took over: no ReLU changes side.
-// The backward products W^T delta use the same trick with the packed transposes.  The weight
-// gradients dW = delta a^T contract over the samples: both operands are read from the slots with
-// samples on the K index and accumulate in registers over all tiles of the wave.  At the end each
-// back wave writes its gradients to its own slice of a partial buffer, reduced in a fixed order
-// afterwards, so parameter gradients do not depend on scheduling.
+// Arithmetic.  FP32 matrix instructions and vector instructions take turns on a SIMD, so products of
+// FP32 factors run on the FP16 matrix cores, each factor split into two FP16 halves as in the split
+// decode (decode_split.h).  Weights have a power of two per layer (AW); the values of a sample have one
+// per layer, from their own largest magnitude, which puts it in [2^11, 2^12): nothing overflows, and
+// samples of any scale keep their 22 bits beside each other.  In a weight gradient, a sum over
+// samples, every sample's inputs are multiplied by the power of two that brings its product to the
+// scale 2^x of the accumulators (exact, or lost far below them); x is the smallest exponent the wave
+// has met, and the back wave rescales its accumulators when it falls.
+//
+// ReLUs.  A unit within rounding of its kink would fall on a side that depends on the arithmetic, and
+// with it a sample's whole gradient.  A tile with such a unit (a pre-activation below 2^-19 of its
+// sample's largest one in the layer, some twenty times the differences measured; about 1% of tiles),
+// or whose output is not finite, runs its forward pass again in FP32 (v_mfma_f32_16x16x4_f32) and takes
+// activations and outputs from there: no ReLU changes side.  Those FP32 sums have a fixed order.  Slot
+// 4g + r of an accumulator's row tile holds neuron 4g + r or, in natural order, neuron 4r + g: then the
+// K steps run over the neurons in ascending order, and as the instruction is a chain of four FMAs in
+// ascending k, the sums are bit for bit those of the vector kernel (train_vec.h), whose shapes (learned
+// frames, width 16, 1 or 4 hidden layers) keep that order.
+//
+// Layouts.  Lane (g, s) = (lane / 16, lane % 16) works on sample s of the tile.  A layer is Y = W X with
+// the weights as the A operand (16 output rows per row tile) and one sample per column; its
+// accumulator leaves lane (g, s) holding row slots 4g..4g+3 of each row tile, which are the next
+// layer's B operand in place (the weights' K order is permuted when they are packed).  The backward
+// products W^T delta read the same blocks transposed (W_1^T and W_out^T are packed).  The weight gradients
+// dW = delta a^T take both operands from the slots, transposed by the LDS read (samples on the K
+// index), and accumulate in registers over all tiles of the wave.  At the end each back wave writes
+// its gradients to its own slice of a partial buffer, reduced in a fixed order afterwards, so
+// parameter gradients do not depend on scheduling.
 //
 // Layer 1 input.  For the fetch, lane (g, s) loads channels 4g..4g+3 of the 8 trilinear taps of
-// sample s (C = 16; for C = 8 lanes g < 2 load).  Without natural order those registers become the
-// K slots (q, g) of layer 1 directly (slot_input; for C = 8 lanes g >= 2 carry the directions), and
-// a constant-1 slot makes the bias part of the weights; in natural order they are transposed across
-// the four lane groups and the bias is the initial accumulator.  Either way a constant-1 column of
-// the input makes the bias gradient one more column of dW_1.
+// sample s (C = 16; for C = 8 lanes g < 2 load): K slots e = 0..3 of its lane group.  Slot 4 + j of
+// group g holds direction input 4j + g; slot 7 of group 0 a constant 1 with no weight, which makes the
+// bias gradient one more column of dW_1.  The FP32 forward's K slots (q, g) are slot_input's, where a
+// constant-1 slot makes the bias part of the weights, or in natural order inputs 4q + g with the
+// bias as the initial accumulator.
 #pragma once
 
+#include "decode_split.h"
 #include "frames.h"
 #include "latent_fetch.h"
 #include "train_internal.h"
@@ -60,25 +75,41 @@ __host__ __device__ constexpr int slot_input(int q, int g) {
     return q < 2 ? C + 4 + q : (q == 2 ? C + 6 : -1);
 }
 
-// A slot matrix holds 16 samples x 64 columns, 16 floats of padding every 4 samples and the 16-byte
-// groups of a 16-column tile exchanged by the sample: the 16-byte writes (a sample's neurons) and the
-// 4-byte reads (a neuron's samples) touch every bank once, and the column tile is an immediate offset.
-constexpr int kSlotMatrix = 16 * 64 + 3 * 16;
-__device__ __forceinline__ int slot_at(int s, int n) {
-    return s * 64 + (s >> 2) * 16 + (n & ~15) + ((((n >> 2) ^ s) & 3) << 2) + (n & 3);
-}
+// A matrix of a slot: 16 samples x 64 columns of FP16 high halves, then of low ones.  The 8-byte groups
+// (4 columns) of a sample are exchanged by the sample, so that the front wave's 8-byte writes (a
+// sample's neurons) and the back wave's transposing 8-byte reads (ds_read_b64_tr_b16: 4 samples of 16
+// neurons per lane group) both take two turns of all banks.  Byte offset of group c4 of sample s:
+constexpr int kPlane = 16 * 64 * 2;
+constexpr int kSlotMatrix = 2 * kPlane;
+__device__ __forceinline__ int slot_group(int s, int c4) { return s * 128 + ((c4 ^ s) & 15) * 8; }
 
-// Operand blocks of the decoder in LDS (floats).  A block of 4 consecutive K steps is 64 lanes x 4
-// floats, one 16-byte read per lane.
+// A handoff: deltas, inputs, and per sample the weight of its deltas in the bias sums.
+struct TmSlot {
+    uint8_t delta[kSlotMatrix];
+    uint8_t input[kSlotMatrix];
+};
+struct TmSlotScale {
+    _Float16 bias_weight[16];
+    int x, xb;                    // weight gradients are summed times 2^x, bias gradients times 2^xb
+};
+
+// The decoder's operand blocks: FP32 blocks of the exact forward (read from memory by the forward
+// kernel and by tiles that need it), then the part that the training kernel keeps in LDS.  Offsets in
+// floats.  An FP32 block of 4 consecutive K steps is 64 lanes x 4 floats.  A block of halves is, per
+// part (high, low, and split_parts' third), the A operand of one v_mfma_f32_16x16x32_f16: 64 lanes x 8
+// halves, K slot (s, g, e) being slot 16 (2s + e / 4) + 4g + e % 4 of the previous layer's accumulator
+// (decode_mfma.h); the operands of W_k^T are read out of the same blocks by transposing LDS reads.  W_out's blocks hold their first 8 rows only (32 x 16 bytes), W_out^T's are operands
+// of v_mfma_f32_16x16x16_f16 (K slot 4g + e = output) of their first two lane groups (32 x 8 bytes).
 template <int C, int H, int NH, int NF>
 struct TrainLayout {
     static constexpr bool NAT = NF > 0 || H == 16 || NH == 1 || NH == 4;   // natural neuron order
     static constexpr int IN = C + 6 * (NF > 1 ? NF : 1);
     static constexpr int NP1 = 6 * NF * (C + 1);   // frame-layer parameters ahead of the decoder's
     static constexpr int HT = H / 16;              // row tiles of a hidden layer
-    static constexpr int Q1 = NAT ? (IN + 3) / 4 : (C + 8) / 4;   // K steps of layer 1
+    static constexpr int KS = (H + 31) / 32;       // K steps of 32 over a hidden layer
+    static constexpr int P = split_parts(H);       // parts of a block after layer 1
+    static constexpr int Q1 = NAT ? (IN + 3) / 4 : (C + 8) / 4;   // FP32 K steps of layer 1
     static constexpr int G1 = (Q1 + 3) / 4;        // groups of 4 K steps of layer 1
-    static constexpr int NCT1 = (IN + 16) / 16;    // column tiles of dW_1 (inputs, 1, padding)
     static constexpr int NR1 = NF > 0 ? (IN + 15) / 16 : 1;       // row tiles of W_1^T delta_1
     static constexpr int FW1 = 0;                                  // [t'][grp][lane][4]
     static constexpr int FWH = FW1 + HT * G1 * 256;                // layers 2..NH: [t'][t][lane][4]
@@ -87,18 +118,20 @@ struct TrainLayout {
     static constexpr int BIAS = FWO + HT * 256;                    // layers 1..NH, output: [t][g][4]
     static constexpr int FF = BIAS + NH * HT * 16 + 16;            // frame layer: [channel / 4][lane]
     static constexpr int FFB = FF + (NF > 0 ? C / 4 * 64 : 0);     // its biases
-    static constexpr int FWD = FFB + (NF > 0 ? 16 : 0);            // end of the forward part
-    static constexpr int NKO = NF > 0 ? 3 : 4;                     // K steps of W_out^T (outputs 4g + r)
-    static constexpr int BWO = FWD;                                // W_out^T: [t'][r][lane]
-    static constexpr int BWH = BWO + HT * NKO * 64;                 // W_k^T, k = 2..NH: [t'][t][lane][4]
-    static constexpr int BW1 = BWH + (NH - 1) * WH_SZ;             // W_1^T: [u][t][lane][4]
-    static constexpr int BF = BW1 + NR1 * HT * 256;                // frame layer transposed: [q][lane]
-    static constexpr int BLOB = BF + (NF > 0 ? 3 * 64 : 0);
-    static constexpr int SLOT = 2 * kSlotMatrix;   // deltas, inputs
+    static constexpr int FWD = FFB + (NF > 0 ? 16 : 0);            // end of the forward kernel's part
+    static constexpr int BF = FWD;                                 // frame layer transposed: [q][lane]
+    static constexpr int AW = BF + (NF > 0 ? 3 * 64 : 0);          // exponents of the layers' weight scales
+    static constexpr int BLOCKS = AW + 8;                          // blocks of halves
+    static constexpr int A1 = BLOCKS;                              // [j][3 parts][256]
+    static constexpr int AH = A1 + HT * 3 * 256;                   // [k][j][s][P][256]
+    static constexpr int AH_SZ = HT * KS * P * 256;
+    static constexpr int AO = AH + (NH - 1) * AH_SZ;               // [s][P][128]
+    static constexpr int BO = AO + KS * P * 128;                   // W_out^T: [j][P][64]
+    static constexpr int B1 = BO + HT * P * 64;                    // W_1^T: [u][s][P][256]
+    static constexpr int BLOB = B1 + NR1 * KS * P * 256;
+    static constexpr int LDS_FLOATS = BLOB - BIAS;                 // the training kernel's part
     static constexpr int XCH = NF > 0 ? 16 * 12 : 0;   // per front wave: values handed across lanes
-    static constexpr int LDS_FLOATS = BLOB + 4 * (2 * SLOT + XCH);
-    static constexpr bool FITS = LDS_FLOATS * 4 + 16 * 16 + 64 <= 160 * 1024;
-    static_assert(FWD % 4 == 0 && BLOB % 4 == 0, "16-byte alignment of blocks");
+    static_assert(BIAS % 4 == 0 && FWD % 4 == 0 && BLOCKS % 4 == 0 && BLOB % 4 == 0, "16-byte alignment of blocks");
 };
 
 // Neuron of row slot i of a row tile (an involution).

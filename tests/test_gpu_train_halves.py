@@ -1,0 +1,90 @@
+"""The training kernel's products in FP16 halves (csrc/train_mfma.h) against FP64 autograd: samples
+whose gradients differ by many powers of two in one tile (each has its own scale), and sums over many
+samples of either sign (a rounding that leans to one side would add up in them; with given output
+gradients, as the FP32 softplus of a loss leans by itself).
+
+Samples with a hidden unit within 1e-5 of its kink are left out (a NaN code or query contributes
+nothing), so that every ReLU is on the same side in FP64.  Tolerances: a pair of halves holds 22 bits of
+a sample's largest value, so each of the at most nine products in a row is within 2^-21 of it times the
+root of 64 terms at worst, 3e-5 together, for one sample's gradient; sums over samples of independent
+errors of 2^-24 stay within 1e-6 of their norm, where a bias of 1/5 of that would reach 3e-6 at 65,536.
+"""
+import numpy as np
+import pytest
+
+from paper_2305_02678_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    assert t.cuda.is_available()
+    return t
+
+
+@pytest.fixture(scope="module")
+def nam(torch):
+    from paper_2305_02678_amd import nam as n
+    n.lib()
+    return n
+
+
+def _case(torch, nam, C, hidden, n, seed):
+    """Model, queries and their codes, which samples are not near a kink, and the FP64 network."""
+    r = wl.rngs(seed)
+    m = wl.make_material(r[0], r[1], 16, 16, C, 3, hidden)
+    m.params = (m.params + 0.05 * r[1].standard_normal(m.params.size)).astype(np.float32)
+    q = wl.uniform_queries(r[2], n, 0.0, 1.0)
+    at = r[3].integers(0, 16, (n, 2))                    # a texel of level 0 and its centre
+    z = torch.from_numpy(np.ascontiguousarray(m.levels[0], np.float32)[at[:, 1], at[:, 0]])
+    q.uv[:], q.lod[:] = (at + 0.5) / 16, 0.0
+    p64 = torch.from_numpy(m.params).double().requires_grad_()
+
+    def net(zz):
+        x, o, margin = torch.cat([zz, torch.from_numpy(q.wi).double(), torch.from_numpy(q.wo).double()], 1), 0, None
+        for k, (a, b) in enumerate(zip(m.dims[:-1], m.dims[1:])):
+            y = x @ p64[o:o + a * b].view(b, a).T + p64[o + a * b:o + a * b + b]
+            o += a * b + b
+            if k < len(m.dims) - 2:
+                near = (y.abs().min(1).values / y.abs().max(1).values).detach()
+                margin = near if margin is None else torch.minimum(margin, near)
+                x = y.relu()
+        return torch.nn.functional.softplus(y), margin
+
+    keep = net(z.double())[1] > 1e-5
+    assert keep.float().mean() > 0.9
+    model = nam.Model.from_workload(nam.Context(0), m)
+    tex, par = (torch.from_numpy(np.ascontiguousarray(v, np.float32)).cuda() for v in (nam.concat_levels(m.levels), m.params))
+    return model, tex, par, q, z, keep, net, p64
+
+
+@pytest.mark.parametrize("C,hidden", [(16, [64] * 3), (8, [32] * 2), (16, [16] * 2), (8, [64])])
+def test_samples_of_different_scale(nam, torch, C, hidden):
+    n = 333
+    model, _, par, q, z, keep, net, p64 = _case(torch, nam, C, hidden, n, 91)
+    k = torch.from_numpy(np.random.default_rng(92).integers(0, 60, (n, 1)))
+    target = (-torch.exp2(k.double())).float().expand(n, 3).contiguous()
+    zz = z.double().requires_grad_()
+    e = torch.where(keep[:, None], net(zz)[0] - target.double(), 0.0)
+    dz, dp = torch.autograd.grad((e ** 2).sum() / e.numel(), (zz, p64))
+    z[~keep] = float("nan")
+    dev = [torch.from_numpy(np.ascontiguousarray(v, np.float32)).cuda() for v in (z.numpy(), q.wi, q.wo)]
+    _, gz, gp = model.loss_backward_codes(par, *dev, target.cuda())
+    gz = gz.cpu().double()
+    assert (gz[~keep] == 0).all()
+    err = ((gz - dz).norm(dim=1) / dz.norm(dim=1))[keep]
+    assert err.max() <= 3e-5
+    assert (gp.cpu().double() - dp).norm() <= 3e-5 * dp.norm()
+
+
+@pytest.mark.parametrize("C,hidden", [(16, [64] * 3), (8, [32] * 2), (16, [16] * 2)])
+def test_sums_over_either_sign(nam, torch, C, hidden):
+    n = 65536
+    model, tex, par, q, z, keep, net, p64 = _case(torch, nam, C, hidden, n, 93)
+    d_rgb = torch.from_numpy(np.random.default_rng(94).standard_normal((n, 3)).astype(np.float32))
+    dp, = torch.autograd.grad((net(z.double())[0] * torch.where(keep[:, None], d_rgb.double(), 0.0)).sum(), p64)
+    q.uv[~keep.numpy()] = np.nan
+    gp = model.backward(tex, par, *nam.to_device(q), d_rgb.cuda())[1]
+    assert (gp.cpu().double() - dp).norm() <= 1e-6 * dp.norm()

@@ -9,12 +9,7 @@
 // every level: the latent texture's initialisation).  The weights are wave-uniform reads.
 //
 // encoder_backward_kernel: the encoder's share of the first training phase, the gradient of
-// sum_i dz_i . E(filtered parameters at query i).  One wave per workgroup, one sample per lane
-// for the forward and the deltas, every layer's activations in the lane's LDS column; the layers
-// are walked down, and each layer's weight gradient, a contraction over the samples, runs on the
-// FP32 matrix cores from those columns (grad_mfma), accumulated in registers over all of the
-// wave's chunks and written once into the workgroup's own partial slice, which is reduced over
-// workgroups in a fixed order afterwards.
+// sum_i dz_i . E(filtered parameters at query i), on the FP32 matrix cores (below).
 #include "train_vec.h"
 
 namespace nam {
@@ -25,20 +20,6 @@ typedef const __attribute__((address_space(4))) float* cf32;
 template <int FI, int FO, bool RELU>
 __device__ __forceinline__ void enc_dense(cf32 W, const float* x, float* y) {
     cf32 b = W + FI * FO;
-    #pragma unroll
-    for (int o = 0; o < FO; ++o) {
-        float s = b[o];
-        #pragma unroll
-        for (int j = 0; j < FI; ++j) s = fmaf(W[o * FI + j], x[j], s);
-        y[o] = RELU ? fmaxf(s, 0.0f) : s;
-    }
-}
-
-// The same with the weights in LDS (read at wave-uniform addresses): inside a loop over chunks
-// the scalar form would keep every weight in scalar registers, more than there are.
-template <int FI, int FO, bool RELU>
-__device__ __forceinline__ void enc_dense_lds(const float* W, const float* x, float* y) {
-    const float* b = W + FI * FO;
     #pragma unroll
     for (int o = 0; o < FO; ++o) {
         float s = b[o];
@@ -97,179 +78,251 @@ __global__ void __launch_bounds__(256) encoder_forward_kernel(const EncoderArgs 
     for (int c = 0; c < C; ++c) a.z[(int64_t)i * C + c] = ok ? out[c] : __builtin_nanf("");
 }
 
-// LDS rows of the backward table (row stride kES floats, odd, so that the 16 rows a matrix-core
-// operand reads lie in different banks): the input (A values), the NHE hidden layers (their
-// activations, then their deltas), the output deltas.
-constexpr int kES = kTW + 1;
-
-template <int A, int C, int HE, int NHE>
-struct EncRows {
-    static constexpr int X = 0;
-    static constexpr int hid(int k) { return A + k * HE; }
-    static constexpr int D = A + NHE * HE;
-    static constexpr int TOTAL = D + C;
-};
+// ---- backward
+//
+// Each wave of a workgroup walks its own tiles of 16 samples; lane (g, s) = (lane / 16, lane % 16) works
+// on sample s.  A layer is Y = W X on v_mfma_f32_16x16x4_f32, a chain of FMAs in ascending k, with the
+// weights as the A operand: row slot i of a row tile is neuron 4 (i % 4) + i / 4, so that the accumulator
+// of lane (g, s) holds neurons 4 r + g, the B operand of K step r of the next layer, and the sums run over
+// the neurons in ascending order (bit for bit the forward kernel's, so every ReLU is on its side).  The
+// weights lie in LDS as operands, shared by the workgroup.  A layer's weight gradient is a contraction
+// over the samples: activations and deltas pass through the wave's LDS rows, which give them back
+// with the samples on the K index, and the sums stay in registers over all of the wave's tiles.  At the
+// end the workgroup sums its waves in ascending order into its slice of the partial buffer; the slices
+// are reduced in a fixed order afterwards.
+//
+// What bounds it: FP32 matrix and vector instructions, which take turns on a SIMD: at 4-32-32-16 86 of
+// the former at 32 cycles per tile, 73 us of 2^20 samples.  One sample per lane with the layers on the
+// vector ALU and one wave per SIMD took 371 us; this takes 139 us.
+constexpr int kEncWaves = 8;
+constexpr int kES = 17;                        // LDS row stride: the 16 samples of a tile, one bank apart
 
 typedef float f32x4e __attribute__((ext_vector_type(4)));
 
-// Weight gradient of one layer on the FP32 matrix cores, accumulated over the wave's samples:
-// G[o][j] += sum_s delta[o][s] x[j][s] for o < FO, j <= FI, with x[FI][s] = 1 so that column FI
-// is the bias gradient.  v_mfma_f32_16x16x4f32 tiles of 16 rows x 16 columns, K = 4 samples
-// per instruction, 16 K steps per 64 samples: lane l takes delta[16 r + l % 16][4 k + l / 16]
-// as the A operand and x[16 c + l % 16][4 k + l / 16] as the B operand, straight from the
-// lanes' LDS columns.  The accumulator of tile (r, c) leaves lane l holding rows
-// 16 r + 4 (l / 16) .. + 3 of column 16 c + l % 16.
+template <int A, int C, int HE, int NHE>
+struct EncTile {
+    static constexpr int HT = HE / 16, KA = A / 4, KH = HE / 4, KC = C / 4;   // row tiles, K steps
+    // operand blocks [row tile][K step][lane], then the biases [layer][row tile][g][r]
+    static constexpr int W1 = 0;
+    static constexpr int W2 = W1 + HT * KA * 64;
+    static constexpr int WOT = W2 + (NHE - 1) * HT * KH * 64;                 // W_out^T
+    static constexpr int W2T = WOT + HT * KC * 64;
+    static constexpr int BIAS = W2T + (NHE - 1) * HT * KH * 64;
+    static constexpr int WEIGHTS = BIAS + NHE * HE;
+    // a wave's rows: input, hidden layers (activations, then their deltas), output deltas
+    static constexpr int X = 0;
+    static constexpr int hid(int k) { return A + k * HE; }
+    static constexpr int D = A + NHE * HE;
+    static constexpr int ROWS = D + C;
+    static constexpr int SUM = kEncWaves * 4 * 256;                           // 4 tiles of every wave
+    static constexpr int WORK = WEIGHTS + kEncWaves * ROWS * kES;
+    static constexpr int LDS = WORK > SUM ? WORK : SUM;
+    // packed offsets of the layers
+    static constexpr int off(int k) {
+        return k == 0 ? 0 : (k == NHE ? A * HE + HE + (NHE - 1) * (HE * HE + HE) : A * HE + HE);
+    }
+};
+
+__device__ __forceinline__ int enc_neuron(int i) { return 4 * (i & 3) + (i >> 2); }
+
+// Weight gradient of one layer: G[o][j] += sum_s delta[o][s] x[j][s] for o < FO, j <= FI, with
+// x[FI][s] = 1 so that column FI is the bias gradient.
 template <int FI, int FO>
 struct GradTiles {
     static constexpr int RO = (FO + 15) / 16;
     static constexpr int CJ = (FI + 1 + 15) / 16;
     f32x4e acc[RO][CJ];
+
+    __device__ __forceinline__ void zero() {
+        #pragma unroll
+        for (int r = 0; r < RO; ++r)
+            #pragma unroll
+            for (int c = 0; c < CJ; ++c) acc[r][c] = f32x4e{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+
+    // delta, x: the wave's rows of the layer
+    __device__ __forceinline__ void add(const float* delta, const float* x, int lane) {
+        const int i = lane & 15, g = lane >> 4;
+        #pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int smp = 4 * k + g;
+            float av[RO], bv[CJ];
+            #pragma unroll
+            for (int r = 0; r < RO; ++r) {
+                const int o = 16 * r + i;
+                av[r] = o < FO ? delta[o * kES + smp] : 0.0f;
+            }
+            #pragma unroll
+            for (int c = 0; c < CJ; ++c) {
+                const int j = 16 * c + i;
+                bv[c] = j < FI ? x[j * kES + smp] : (j == FI ? 1.0f : 0.0f);
+            }
+            #pragma unroll
+            for (int r = 0; r < RO; ++r)
+                #pragma unroll
+                for (int c = 0; c < CJ; ++c)
+                    acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[r], bv[c], acc[r][c], 0, 0, 0);
+        }
+    }
+
+    // The workgroup's sum into the packed slice (W[FO][FI], then b[FO]), four tiles at a time.
+    __device__ __forceinline__ void store(float* sum, float* part, int wave, int lane) const {
+        #pragma unroll
+        for (int first = 0; first < RO * CJ; first += 4) {
+            __syncthreads();
+            #pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (first + u < RO * CJ)
+                    *reinterpret_cast<f32x4e*>(sum + ((wave * 4 + u) * 64 + lane) * 4) = acc[(first + u) / CJ][(first + u) % CJ];
+            __syncthreads();
+            const int tile = first + wave, r = tile / CJ, c = tile % CJ;
+            if (wave < 4 && tile < RO * CJ) {
+                f32x4e v = {0.0f, 0.0f, 0.0f, 0.0f};
+                #pragma unroll
+                for (int w = 0; w < kEncWaves; ++w)
+                    v += *reinterpret_cast<const f32x4e*>(sum + ((w * 4 + wave) * 64 + lane) * 4);
+                #pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int o = 16 * r + 4 * (lane >> 4) + e, j = 16 * c + (lane & 15);
+                    if (o < FO && j < FI) part[o * FI + j] = v[e];
+                    else if (o < FO && j == FI) part[FI * FO + o] = v[e];
+                }
+            }
+        }
+    }
 };
 
-template <int FI, int FO>
-__device__ __forceinline__ void grad_mfma(const float* lds, int drow, int arow, int lane, GradTiles<FI, FO>& G) {
-    const int i = lane & 15, q = lane >> 4;
-    #pragma unroll 1
-    for (int k = 0; k < kTW / 4; ++k) {
-        const int smp = 4 * k + q;
-        float av[GradTiles<FI, FO>::RO], bv[GradTiles<FI, FO>::CJ];
-        #pragma unroll
-        for (int r = 0; r < GradTiles<FI, FO>::RO; ++r) {
-            const int o = 16 * r + i;
-            av[r] = o < FO ? lds[(drow + o) * kES + smp] : 0.0f;
-        }
-        #pragma unroll
-        for (int c = 0; c < GradTiles<FI, FO>::CJ; ++c) {
-            const int j = 16 * c + i;
-            bv[c] = j < FI ? lds[(arow + j) * kES + smp] : (j == FI ? 1.0f : 0.0f);
-        }
-        #pragma unroll
-        for (int r = 0; r < GradTiles<FI, FO>::RO; ++r)
-            #pragma unroll
-            for (int c = 0; c < GradTiles<FI, FO>::CJ; ++c)
-                G.acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[r], bv[c], G.acc[r][c], 0, 0, 0);
-    }
-}
-
-// The layer's gradient into the packed slice (W[FO][FI], then b[FO]), every entry written once.
-template <int FI, int FO>
-__device__ __forceinline__ void grad_store(const GradTiles<FI, FO>& G, float* part, int lane) {
-    const int col = lane & 15, g = lane >> 4;
+// acc[t] += W b over K steps, blocks at w
+template <int HT, int K>
+__device__ __forceinline__ void enc_layer(const float* w, const float* b, f32x4e* acc, int lane) {
     #pragma unroll
-    for (int r = 0; r < GradTiles<FI, FO>::RO; ++r)
+    for (int q = 0; q < K; ++q)
         #pragma unroll
-        for (int c = 0; c < GradTiles<FI, FO>::CJ; ++c)
-            #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int o = 16 * r + 4 * g + e, j = 16 * c + col;
-                if (o < FO && j < FI) part[o * FI + j] = G.acc[r][c][e];
-                else if (o < FO && j == FI) part[FI * FO + o] = G.acc[r][c][e];
-            }
+        for (int t = 0; t < HT; ++t)
+            acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[(t * K + q) * 64 + lane], b[q], acc[t], 0, 0, 0);
 }
 
-template <int FI, int FO>
-__device__ __forceinline__ void grad_zero(GradTiles<FI, FO>& G) {
-    #pragma unroll
-    for (int r = 0; r < GradTiles<FI, FO>::RO; ++r)
-        #pragma unroll
-        for (int c = 0; c < GradTiles<FI, FO>::CJ; ++c) G.acc[r][c] = f32x4e{0.0f, 0.0f, 0.0f, 0.0f};
-}
-
+// Waves per SIMD: at width 64 the gradients' registers leave room for two.
 template <int A, int C, int HE, int NHE>
-__global__ void __launch_bounds__(kTW) encoder_backward_kernel(const EncoderArgs a) {
-    using R = EncRows<A, C, HE, NHE>;
-    constexpr int NP = A * HE + HE + (NHE - 1) * (HE * HE + HE) + HE * C + C;
-    __shared__ float lds[R::TOTAL * kES];
-    __shared__ float wl[NP];                   // the encoder's parameters
+__global__ void __launch_bounds__(64 * kEncWaves, HE == 64 ? 2 : 4) encoder_backward_kernel(const EncoderArgs a) {
+    using L = EncTile<A, C, HE, NHE>;
+    constexpr int HT = L::HT;
+    __shared__ __attribute__((aligned(16))) float lds[L::LDS];
     __shared__ LevelRow rows[kMaxLevels];
-    const int lane = threadIdx.x;
-    if (lane < a.M) rows[lane] = a.rows[lane];
-    for (int p = lane; p < NP; p += kTW) wl[p] = a.params[p];
-    float* col = lds + lane;
-    lds_sync_wave();
-
-    int off[NHE + 1];                          // packed offsets of the layers
-    {
-        int o = 0;
-        #pragma unroll
-        for (int k = 0; k <= NHE; ++k) {
-            off[k] = o;
-            const int fi = k == 0 ? A : HE, fo = k == NHE ? C : HE;
-            o += fi * fo + fo;
+    const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, s = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (tid < a.M) rows[tid] = a.rows[tid];
+    const float* P2 = a.params + L::off(1);
+    const float* PO = a.params + L::off(NHE);
+    for (int e = tid; e < L::WEIGHTS; e += 64 * kEncWaves) {
+        const int eg = (e >> 4) & 3, ei = enc_neuron(e & 15);
+        float v;
+        if (e < L::W2) {
+            const int b = e >> 6, q = b % L::KA, t = b / L::KA;
+            v = a.params[(16 * t + ei) * A + 4 * q + eg];
+        } else if (e < L::WOT) {
+            const int b = (e - L::W2) >> 6, q = b % L::KH, t = b / L::KH;
+            v = P2[(16 * t + ei) * HE + 4 * q + eg];
+        } else if (e < L::W2T) {
+            const int b = (e - L::WOT) >> 6, q = b % L::KC, t = b / L::KC;
+            v = PO[(4 * q + eg) * HE + 16 * t + ei];
+        } else if (e < L::BIAS) {
+            const int b = (e - L::W2T) >> 6, q = b % L::KH, t = b / L::KH;
+            v = P2[(4 * q + eg) * HE + 16 * t + ei];
+        } else {
+            const int k = (e - L::BIAS) / HE, y = (e - L::BIAS) % HE, o = (y & ~15) + 4 * (y & 3) + ((y >> 2) & 3);
+            v = k == 0 ? a.params[A * HE + o] : P2[HE * HE + o];
         }
+        lds[e] = v;
     }
-    // the wave's gradients, accumulated over all its chunks in matrix-core accumulators
+    __syncthreads();
+    float* table = lds + L::WEIGHTS + wave * L::ROWS * kES;
     GradTiles<A, HE> g0;
     GradTiles<HE, HE> gh;                      // the hidden-to-hidden layer (NHE = 2)
     GradTiles<HE, C> go;
-    grad_zero(g0);
-    grad_zero(gh);
-    grad_zero(go);
-    const int nchunks = (a.n + kTW - 1) / kTW;
-    for (int c = blockIdx.x; c < nchunks; c += gridDim.x) {
-        const int i = c * kTW + lane;
-        const bool in_range = i < a.n;
-        const int ic = in_range ? i : a.n - 1;
-        // ---- input and forward (a sample that contributes nothing has zero input and delta)
-        float x[A];
-        const bool live = enc_input<A, true>(a, rows, ic, x) && in_range;
+    g0.zero();
+    gh.zero();
+    go.zero();
+    const int tiles = (a.n - 1) / 16 + 1, waves = gridDim.x * kEncWaves;
+    // consecutive tiles on different workgroups: a small batch spreads over the CUs
+    for (int tile = wave * gridDim.x + blockIdx.x; tile < tiles; tile += waves) {
+        asm volatile("" ::: "memory");         // the weights are read per tile, not kept in registers
+        const int64_t i = (int64_t)tile * 16 + s;
+        const int ic = i < a.n ? (int)i : a.n - 1;
+        // ---- input (attributes 4q + g): a sample that contributes nothing has zero input and delta
+        float x[L::KA], d[L::KC];
+        const float2 q2 = reinterpret_cast<const float2*>(a.uv)[ic];
+        const float lod = a.lod[ic];
+        const bool live = query_ok(q2.x, q2.y, lod) && i < a.n;
+        Taps t;
+        query_taps_rows(rows, a.M, a.address, q2.x, q2.y, lod, t);
         #pragma unroll
-        for (int j = 0; j < A; ++j) {
-            x[j] = live ? x[j] : 0.0f;
-            col[(R::X + j) * kES] = x[j];
-        }
-        {
-            float h[HE];
-            enc_dense_lds<A, HE, true>(wl + off[0], x, h);
+        for (int q = 0; q < L::KC; ++q) d[q] = a.dz[(int64_t)ic * C + 4 * q + g];
+        #pragma unroll
+        for (int q = 0; q < L::KA; ++q) x[q] = 0.0f;
+        #pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const float* T = a.attrs + t.idx[k] * A + g;
             #pragma unroll
-            for (int o = 0; o < HE; ++o) col[(R::hid(0) + o) * kES] = h[o];
-            if (NHE == 2) {
-                float h2[HE];
-                enc_dense_lds<HE, HE, true>(wl + off[1], h, h2);
-                #pragma unroll
-                for (int o = 0; o < HE; ++o) col[(R::hid(1) + o) * kES] = h2[o];
+            for (int q = 0; q < L::KA; ++q) x[q] = fmaf(t.w[k], T[4 * q], x[q]);
+        }
+        #pragma unroll
+        for (int q = 0; q < L::KA; ++q) {
+            x[q] = live ? x[q] : 0.0f;
+            table[(L::X + 4 * q + g) * kES + s] = x[q];
+        }
+        #pragma unroll
+        for (int q = 0; q < L::KC; ++q) {
+            d[q] = live ? d[q] : 0.0f;
+            table[(L::D + 4 * q + g) * kES + s] = d[q];
+        }
+        // ---- forward
+        float act[NHE][HE / 4];                // K step 4t + r: neuron 16t + 4r + g
+        f32x4e acc[HT];
+        #pragma unroll
+        for (int k = 0; k < NHE; ++k) {
+            #pragma unroll
+            for (int u = 0; u < HT; ++u) acc[u] = *reinterpret_cast<const f32x4e*>(lds + L::BIAS + (k * HT + u) * 16 + 4 * g);
+            if (k == 0) enc_layer<HT, L::KA>(lds + L::W1, x, acc, lane);
+            else enc_layer<HT, L::KH>(lds + L::W2, act[0], acc, lane);
+            #pragma unroll
+            for (int j = 0; j < HE / 4; ++j) {
+                act[k][j] = fmaxf(acc[j / 4][j % 4], 0.0f);
+                table[(L::hid(k) + 4 * j + g) * kES + s] = act[k][j];
             }
         }
-        // ---- output deltas: the given code gradient (the output layer is linear)
-        #pragma unroll
-        for (int cc = 0; cc < C; ++cc) col[(R::D + cc) * kES] = live ? a.dz[(int64_t)ic * C + cc] : 0.0f;
         lds_sync_wave();
         // ---- layers from the output down: weight gradient, then the deltas of the layer below
-        int drow = R::D;
+        go.add(table + L::D * kES, table + L::hid(NHE - 1) * kES, lane);
+        float dh[HE / 4];
         #pragma unroll
-        for (int k = NHE; k >= 0; --k) {
-            const int arow = k == 0 ? R::X : R::hid(k - 1);
-            if (k == NHE) grad_mfma<HE, C>(lds, drow, arow, lane, go);
-            else if (k == 0) grad_mfma<A, HE>(lds, drow, arow, lane, g0);
-            else grad_mfma<HE, HE>(lds, drow, arow, lane, gh);
-            if (k == 0) break;
-            // delta of hidden layer k - 1: (W_k^T delta_k) masked by its ReLU
-            float dprev[HE];
-            {
-                const int FO = k == NHE ? C : HE;
-                const float* W = wl + off[k];
-                #pragma unroll
-                for (int j = 0; j < HE; ++j) dprev[j] = 0.0f;
-                for (int o = 0; o < FO; ++o) {
-                    const float d = col[(drow + o) * kES];
-                    #pragma unroll
-                    for (int j = 0; j < HE; ++j) dprev[j] = fmaf(W[o * HE + j], d, dprev[j]);
-                }
-                #pragma unroll
-                for (int j = 0; j < HE; ++j) dprev[j] = col[(arow + j) * kES] > 0.0f ? dprev[j] : 0.0f;
-            }
-            lds_sync_wave();                       // the gradient has read the activations
+        for (int k = NHE - 1; k >= 0; --k) {
             #pragma unroll
-            for (int j = 0; j < HE; ++j) col[(arow + j) * kES] = dprev[j];
+            for (int u = 0; u < HT; ++u) acc[u] = f32x4e{0.0f, 0.0f, 0.0f, 0.0f};
+            if (k == NHE - 1) enc_layer<HT, L::KC>(lds + L::WOT, d, acc, lane);
+            else enc_layer<HT, L::KH>(lds + L::W2T, dh, acc, lane);
+            lds_sync_wave();                   // the gradient has read the activations
+            #pragma unroll
+            for (int j = 0; j < HE / 4; ++j) {
+                dh[j] = act[k][j] > 0.0f ? acc[j / 4][j % 4] : 0.0f;
+                table[(L::hid(k) + 4 * j + g) * kES + s] = dh[j];
+            }
             lds_sync_wave();
-            drow = arow;
+            if (k == 0) g0.add(table + L::hid(0) * kES, table + L::X * kES, lane);
+            else gh.add(table + L::hid(k) * kES, table + L::hid(0) * kES, lane);
         }
-        lds_sync_wave();                           // the table is free for the next chunk
+        lds_sync_wave();                       // the rows are free for the next tile
     }
     float* part = a.partial + (size_t)blockIdx.x * a.np;
-    grad_store(g0, part + off[0], lane);
-    if (NHE == 2) grad_store(gh, part + off[1], lane);
-    grad_store(go, part + off[NHE], lane);
+    g0.store(lds, part + L::off(0), wave, lane);
+    if (NHE == 2) gh.store(lds, part + L::off(1), wave, lane);
+    go.store(lds, part + L::off(NHE), wave, lane);
+}
+
+// Four tiles per workgroup at least: fewer slices, and a small batch has a wave per SIMD on each CU.
+int encoder_backward_grid(int64_t n, int HE, int cu_count) {
+    const int64_t quads = (n + 63) / 64, most = (int64_t)cu_count * (HE == 64 ? 1 : 2);
+    return (int)(quads < most ? quads : most);
 }
 
 template <int A, int C, int HE, int NHE>
@@ -278,7 +331,7 @@ static hipError_t launch_encoder_shape(int mode, const EncoderArgs& a, int grid,
     const unsigned blocks = (unsigned)((a.n + 255) / 256);
     if (mode == 0) encoder_forward_kernel<A, C, HE, NHE, false><<<blocks, 256, 0, s>>>(a);
     else if (mode == 1) encoder_forward_kernel<A, C, HE, NHE, true><<<blocks, 256, 0, s>>>(a);
-    else encoder_backward_kernel<A, C, HE, NHE><<<grid, kTW, 0, s>>>(a);
+    else encoder_backward_kernel<A, C, HE, NHE><<<grid, 64 * kEncWaves, 0, s>>>(a);
     return hipGetLastError();
 }
 

@@ -484,10 +484,8 @@ static nam_status encoder_run(nam_ctx* ctx, const nam_mlp_desc* enc, const float
         NAM_HIP(launch_fill_f32(d_eparams, np, 0.0f, st));
         return NAM_OK;
     }
-    // one wave per workgroup; a partial slice per workgroup, reduced in a fixed order
-    const int64_t nchunks = (n + 63) / 64;
-    int grid = ctx->cu_count * 4;
-    if (grid > nchunks) grid = (int)nchunks;
+    // a partial slice per workgroup, reduced in a fixed order
+    const int grid = encoder_backward_grid(n, HE, ctx->cu_count);
     s = grow(&ctx->train_ws, &ctx->train_ws_bytes, (size_t)grid * np * 4);
     if (s != NAM_OK) return s;
     a.partial = static_cast<float*>(ctx->train_ws);

@@ -1,103 +1,164 @@
-// The encoder of Sec. 5.1 on the vector ALU, FP32: an MLP from the parameters of the original
+// The encoder of Sec. 5.1 on the FP32 matrix cores: an MLP from the parameters of the original
 // material at a location (A attributes: albedo, roughness, ...) to the latent code (C
 // channels), ReLU hidden layers and a linear output layer.  Its weights are packed as the
 // decoder's (W_1[HE][A], b_1, ..., W_out[C][HE], b_out).
 //
-// encoder_forward_kernel: one item per lane.  For queries the parameters are first filtered
-// at (uv, lod) with the latent fetch's trilinear taps over a pyramid of the parameters (levels
-// concatenated, [texel][A]); the bake instead takes parameter rows as given (every texel of
-// every level: the latent texture's initialisation).  The weights are wave-uniform reads.
+// Each wave of a workgroup walks its own tiles of 16 items; lane (g, s) = (lane / 16, lane % 16) works
+// on item s.  A layer is Y = W X on v_mfma_f32_16x16x4_f32, a chain of FMAs in ascending k, with the
+// weights as the A operand: row slot i of a row tile is neuron 4 (i % 4) + i / 4, so that the accumulator
+// of lane (g, s) holds neurons 4 r + g, the B operand of K step r of the next layer, and the sums run over
+// the neurons in ascending order.  The weights lie in LDS as operands, shared by the workgroup.
+//
+// encoder_forward_kernel: for queries the parameters are first filtered at (uv, lod) with the latent
+// fetch's trilinear taps over a pyramid of the parameters (levels concatenated, [texel][A]); the bake
+// instead takes parameter rows as given (every texel of every level: the latent texture's
+// initialisation).
 //
 // encoder_backward_kernel: the encoder's share of the first training phase, the gradient of
-// sum_i dz_i . E(filtered parameters at query i), on the FP32 matrix cores (below).
+// sum_i dz_i . E(filtered parameters at query i).
 #include "train_vec.h"
 
 namespace nam {
 
-typedef const __attribute__((address_space(4))) float* cf32;
+typedef float f32x4e __attribute__((ext_vector_type(4)));
 
-// y[o] = b[o] + sum_j W[o][j] x[j] (W packed [FO][FI], b after it; wave-uniform)
-template <int FI, int FO, bool RELU>
-__device__ __forceinline__ void enc_dense(cf32 W, const float* x, float* y) {
-    cf32 b = W + FI * FO;
+__device__ __forceinline__ int enc_neuron(int i) { return 4 * (i & 3) + (i >> 2); }
+
+// acc[t] += W b over K steps, blocks at w
+template <int HT, int K>
+__device__ __forceinline__ void enc_layer(const float* w, const float* b, f32x4e* acc, int lane) {
     #pragma unroll
-    for (int o = 0; o < FO; ++o) {
-        float s = b[o];
+    for (int q = 0; q < K; ++q)
         #pragma unroll
-        for (int j = 0; j < FI; ++j) s = fmaf(W[o * FI + j], x[j], s);
-        y[o] = RELU ? fmaxf(s, 0.0f) : s;
-    }
+        for (int t = 0; t < HT; ++t)
+            acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[(t * K + q) * 64 + lane], b[q], acc[t], 0, 0, 0);
 }
 
-// The parameters of item i: a parameter row, or the trilinear filter of the pyramid at the
-// query; false for a query with a non-finite uv or lod.
+// Attributes 4q + g of an item: of a parameter row, or the trilinear filter of the pyramid at the query;
+// false for a query with a non-finite uv or lod.
 template <int A, bool QUERIES>
-__device__ __forceinline__ bool enc_input(const EncoderArgs& a, const LevelRow* rows, int i, float* x) {
+__device__ __forceinline__ bool enc_input(const EncoderArgs& a, const LevelRow* rows, int i, int g, float* x) {
     if (!QUERIES) {
         #pragma unroll
-        for (int j = 0; j < A; ++j) x[j] = a.attrs[(int64_t)i * A + j];
+        for (int q = 0; q < A / 4; ++q) x[q] = a.attrs[(int64_t)i * A + 4 * q + g];
         return true;
     }
-    const float2 q = reinterpret_cast<const float2*>(a.uv)[i];
+    const float2 uv = reinterpret_cast<const float2*>(a.uv)[i];
     const float l = a.lod[i];
     Taps t;
-    query_taps_rows(rows, a.M, a.address, q.x, q.y, l, t);
+    query_taps_rows(rows, a.M, a.address, uv.x, uv.y, l, t);
     #pragma unroll
-    for (int j = 0; j < A; ++j) x[j] = 0.0f;
+    for (int q = 0; q < A / 4; ++q) x[q] = 0.0f;
     #pragma unroll
     for (int k = 0; k < 8; ++k) {
-        const float* T = a.attrs + t.idx[k] * A;
+        const float* T = a.attrs + t.idx[k] * A + g;
         #pragma unroll
-        for (int j = 0; j < A; ++j) x[j] = fmaf(t.w[k], T[j], x[j]);
+        for (int q = 0; q < A / 4; ++q) x[q] = fmaf(t.w[k], T[4 * q], x[q]);
     }
-    return query_ok(q.x, q.y, l);
+    return query_ok(uv.x, uv.y, l);
 }
 
+// ---- forward
+//
+// What bounds it: the random texels, 8 per item at uniform queries: 2^20 items at 4-32-32-16 over a
+// 1024 x 1024 pyramid of 22 MB take 83 us (one item per lane with the layers on the vector ALU and a
+// code written 64 bytes apart per lane 89 us), the 100,003 of an encoder of width 16 10 us less.
+constexpr int kEncFwdWaves = 4;
+
+template <int A, int C, int HE, int NHE>
+struct EncForward {
+    static constexpr int HT = HE / 16, KA = A / 4, KH = HE / 4;
+    // operand blocks [row tile][K step][lane]; W_out's rows are channels in order; the biases
+    static constexpr int W1 = 0;
+    static constexpr int W2 = W1 + HT * KA * 64;
+    static constexpr int WO = W2 + (NHE - 1) * HT * KH * 64;
+    static constexpr int BIAS = WO + KH * 64;
+    static constexpr int BO = BIAS + NHE * HE;
+    static constexpr int FLOATS = BO + 16;
+};
+
 template <int A, int C, int HE, int NHE, bool QUERIES>
-__global__ void __launch_bounds__(256) encoder_forward_kernel(const EncoderArgs a) {
+__global__ void __launch_bounds__(64 * kEncFwdWaves) encoder_forward_kernel(const EncoderArgs a) {
+    using L = EncForward<A, C, HE, NHE>;
+    constexpr int HT = L::HT;
+    __shared__ __attribute__((aligned(16))) float lds[L::FLOATS];
     __shared__ LevelRow rows[kMaxLevels];
-    if (QUERIES && threadIdx.x < a.M) rows[threadIdx.x] = a.rows[threadIdx.x];
-    if (QUERIES) __syncthreads();
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= a.n) return;
-    float x[A];
-    const bool ok = enc_input<A, QUERIES>(a, rows, i, x);
-    cf32 P = (cf32)a.params;
-    float h[HE], h2[HE], out[C];
-    enc_dense<A, HE, true>(P, x, h);
-    P += A * HE + HE;
-    #pragma unroll
-    for (int k = 1; k < NHE; ++k) {
-        enc_dense<HE, HE, true>(P, h, h2);
-        #pragma unroll
-        for (int o = 0; o < HE; ++o) h[o] = h2[o];
-        P += HE * HE + HE;
+    const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, s = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (QUERIES && tid < a.M) rows[tid] = a.rows[tid];
+    const float* P2 = a.params + A * HE + HE;
+    const float* PO = P2 + (NHE - 1) * (HE * HE + HE);
+    for (int e = tid; e < L::FLOATS; e += 64 * kEncFwdWaves) {
+        const int eg = (e >> 4) & 3, ei = enc_neuron(e & 15);
+        float v;
+        if (e < L::W2) {
+            const int b = e >> 6, q = b % L::KA, t = b / L::KA;
+            v = a.params[(16 * t + ei) * A + 4 * q + eg];
+        } else if (e < L::WO) {
+            const int b = (e - L::W2) >> 6, q = b % L::KH, t = b / L::KH;
+            v = P2[(16 * t + ei) * HE + 4 * q + eg];
+        } else if (e < L::BIAS) {
+            const int q = (e - L::WO) >> 6, o = e & 15;
+            v = o < C ? PO[o * HE + 4 * q + eg] : 0.0f;
+        } else if (e < L::BO) {
+            const int k = (e - L::BIAS) / HE, y = (e - L::BIAS) % HE, o = (y & ~15) + 4 * (y & 3) + ((y >> 2) & 3);
+            v = k == 0 ? a.params[A * HE + o] : P2[HE * HE + o];
+        } else {
+            const int o = e - L::BO;
+            v = o < C ? PO[C * HE + o] : 0.0f;
+        }
+        lds[e] = v;
     }
-    enc_dense<HE, C, false>(P, h, out);
-    #pragma unroll
-    for (int c = 0; c < C; ++c) a.z[(int64_t)i * C + c] = ok ? out[c] : __builtin_nanf("");
+    __syncthreads();
+    const bool wide = (reinterpret_cast<uintptr_t>(a.z) & 15) == 0;
+    const int tiles = (a.n - 1) / 16 + 1, waves = gridDim.x * kEncFwdWaves;
+    // consecutive tiles on different workgroups: a small batch spreads over the CUs
+    for (int tile = wave * gridDim.x + blockIdx.x; tile < tiles; tile += waves) {
+        asm volatile("" ::: "memory");         // the weights are read per tile, not kept in registers
+        const int64_t i = (int64_t)tile * 16 + s;
+        const int ic = i < a.n ? (int)i : a.n - 1;
+        float x[HE / 4 > L::KA ? HE / 4 : L::KA];
+        const bool ok = enc_input<A, QUERIES>(a, rows, ic, g, x);
+        f32x4e acc[HT];
+        #pragma unroll
+        for (int k = 0; k < NHE; ++k) {
+            #pragma unroll
+            for (int u = 0; u < HT; ++u) acc[u] = *reinterpret_cast<const f32x4e*>(lds + L::BIAS + (k * HT + u) * 16 + 4 * g);
+            if (k == 0) enc_layer<HT, L::KA>(lds + L::W1, x, acc, lane);
+            else enc_layer<HT, L::KH>(lds + L::W2, x, acc, lane);
+            #pragma unroll
+            for (int j = 0; j < HE / 4; ++j) x[j] = fmaxf(acc[j / 4][j % 4], 0.0f);
+        }
+        f32x4e z[1] = {*reinterpret_cast<const f32x4e*>(lds + L::BO + 4 * g)};
+        enc_layer<1, L::KH>(lds + L::WO, x, z, lane);
+        if (i < a.n && 4 * g < C) {
+            float* to = a.z + i * C + 4 * g;
+            #pragma unroll
+            for (int r = 0; r < 4; ++r) z[0][r] = ok ? z[0][r] : __builtin_nanf("");
+            if (wide) {
+                *reinterpret_cast<f32x4e*>(to) = z[0];
+            } else {
+                #pragma unroll
+                for (int r = 0; r < 4; ++r) to[r] = z[0][r];
+            }
+        }
+    }
 }
 
 // ---- backward
 //
-// Each wave of a workgroup walks its own tiles of 16 samples; lane (g, s) = (lane / 16, lane % 16) works
-// on sample s.  A layer is Y = W X on v_mfma_f32_16x16x4_f32, a chain of FMAs in ascending k, with the
-// weights as the A operand: row slot i of a row tile is neuron 4 (i % 4) + i / 4, so that the accumulator
-// of lane (g, s) holds neurons 4 r + g, the B operand of K step r of the next layer, and the sums run over
-// the neurons in ascending order (bit for bit the forward kernel's, so every ReLU is on its side).  The
-// weights lie in LDS as operands, shared by the workgroup.  A layer's weight gradient is a contraction
-// over the samples: activations and deltas pass through the wave's LDS rows, which give them back
-// with the samples on the K index, and the sums stay in registers over all of the wave's tiles.  At the
-// end the workgroup sums its waves in ascending order into its slice of the partial buffer; the slices
-// are reduced in a fixed order afterwards.
+// A layer's weight gradient is a contraction over the samples (the activations are bit for bit the forward
+// kernel's): activations and deltas pass through the wave's LDS rows, which give them back with the
+// samples on the K index, and the sums stay in registers over all of the wave's tiles.  At the end the
+// workgroup sums its waves in ascending order into its slice of the partial buffer; the slices are
+// reduced in a fixed order afterwards.
 //
 // What bounds it: FP32 matrix and vector instructions, which take turns on a SIMD: at 4-32-32-16 86 of
 // the former at 32 cycles per tile, 73 us of 2^20 samples.  One sample per lane with the layers on the
-// vector ALU and one wave per SIMD took 371 us; this takes 139 us.
+// vector ALU and one wave per SIMD took 371 us; this takes 144 us, 83 us of it the forward kernel's
+// fetch.
 constexpr int kEncWaves = 8;
 constexpr int kES = 17;                        // LDS row stride: the 16 samples of a tile, one bank apart
-
-typedef float f32x4e __attribute__((ext_vector_type(4)));
 
 template <int A, int C, int HE, int NHE>
 struct EncTile {
@@ -122,8 +183,6 @@ struct EncTile {
         return k == 0 ? 0 : (k == NHE ? A * HE + HE + (NHE - 1) * (HE * HE + HE) : A * HE + HE);
     }
 };
-
-__device__ __forceinline__ int enc_neuron(int i) { return 4 * (i & 3) + (i >> 2); }
 
 // Weight gradient of one layer: G[o][j] += sum_s delta[o][s] x[j][s] for o < FO, j <= FI, with
 // x[FI][s] = 1 so that column FI is the bias gradient.
@@ -192,16 +251,6 @@ struct GradTiles {
     }
 };
 
-// acc[t] += W b over K steps, blocks at w
-template <int HT, int K>
-__device__ __forceinline__ void enc_layer(const float* w, const float* b, f32x4e* acc, int lane) {
-    #pragma unroll
-    for (int q = 0; q < K; ++q)
-        #pragma unroll
-        for (int t = 0; t < HT; ++t)
-            acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[(t * K + q) * 64 + lane], b[q], acc[t], 0, 0, 0);
-}
-
 // Waves per SIMD: at width 64 the gradients' registers leave room for two.
 template <int A, int C, int HE, int NHE>
 __global__ void __launch_bounds__(64 * kEncWaves, HE == 64 ? 2 : 4) encoder_backward_kernel(const EncoderArgs a) {
@@ -251,21 +300,9 @@ __global__ void __launch_bounds__(64 * kEncWaves, HE == 64 ? 2 : 4) encoder_back
         const int ic = i < a.n ? (int)i : a.n - 1;
         // ---- input (attributes 4q + g): a sample that contributes nothing has zero input and delta
         float x[L::KA], d[L::KC];
-        const float2 q2 = reinterpret_cast<const float2*>(a.uv)[ic];
-        const float lod = a.lod[ic];
-        const bool live = query_ok(q2.x, q2.y, lod) && i < a.n;
-        Taps t;
-        query_taps_rows(rows, a.M, a.address, q2.x, q2.y, lod, t);
+        const bool live = enc_input<A, true>(a, rows, ic, g, x) && i < a.n;
         #pragma unroll
         for (int q = 0; q < L::KC; ++q) d[q] = a.dz[(int64_t)ic * C + 4 * q + g];
-        #pragma unroll
-        for (int q = 0; q < L::KA; ++q) x[q] = 0.0f;
-        #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const float* T = a.attrs + t.idx[k] * A + g;
-            #pragma unroll
-            for (int q = 0; q < L::KA; ++q) x[q] = fmaf(t.w[k], T[4 * q], x[q]);
-        }
         #pragma unroll
         for (int q = 0; q < L::KA; ++q) {
             x[q] = live ? x[q] : 0.0f;
@@ -319,7 +356,12 @@ __global__ void __launch_bounds__(64 * kEncWaves, HE == 64 ? 2 : 4) encoder_back
     go.store(lds, part + L::off(NHE), wave, lane);
 }
 
-// Four tiles per workgroup at least: fewer slices, and a small batch has a wave per SIMD on each CU.
+// Four tiles per workgroup at least (backward: fewer slices); a small batch has a wave per SIMD on each CU.
+int encoder_forward_grid(int64_t n, int cu_count) {
+    const int64_t quads = (n + 63) / 64, most = (int64_t)cu_count * 5;
+    return (int)(quads < most ? quads : most);
+}
+
 int encoder_backward_grid(int64_t n, int HE, int cu_count) {
     const int64_t quads = (n + 63) / 64, most = (int64_t)cu_count * (HE == 64 ? 1 : 2);
     return (int)(quads < most ? quads : most);
@@ -328,9 +370,8 @@ int encoder_backward_grid(int64_t n, int HE, int cu_count) {
 template <int A, int C, int HE, int NHE>
 static hipError_t launch_encoder_shape(int mode, const EncoderArgs& a, int grid, hipStream_t s) {
     clear_stale_hip_error();
-    const unsigned blocks = (unsigned)((a.n + 255) / 256);
-    if (mode == 0) encoder_forward_kernel<A, C, HE, NHE, false><<<blocks, 256, 0, s>>>(a);
-    else if (mode == 1) encoder_forward_kernel<A, C, HE, NHE, true><<<blocks, 256, 0, s>>>(a);
+    if (mode == 0) encoder_forward_kernel<A, C, HE, NHE, false><<<grid, 64 * kEncFwdWaves, 0, s>>>(a);
+    else if (mode == 1) encoder_forward_kernel<A, C, HE, NHE, true><<<grid, 64 * kEncFwdWaves, 0, s>>>(a);
     else encoder_backward_kernel<A, C, HE, NHE><<<grid, 64 * kEncWaves, 0, s>>>(a);
     return hipGetLastError();
 }

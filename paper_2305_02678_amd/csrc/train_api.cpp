@@ -477,7 +477,7 @@ static nam_status encoder_run(nam_ctx* ctx, const nam_mlp_desc* enc, const float
     hipStream_t st = (hipStream_t)stream;
     if (mode < 2) {
         if (n == 0) return NAM_OK;
-        NAM_HIP(launch_encoder(A, C, HE, NHE, mode, a, 0, st));
+        NAM_HIP(launch_encoder(A, C, HE, NHE, mode, a, encoder_forward_grid(n, ctx->cu_count), st));
         return NAM_OK;
     }
     if (n == 0) {

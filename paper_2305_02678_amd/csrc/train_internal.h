@@ -113,6 +113,7 @@ bool encoder_shape_supported(int A, int C, int HE, int NHE);
 // mode 0: the encoder on parameter rows; 1: on the parameters filtered at queries; 2: the
 // gradient of its parameters into a.partial (grid workgroups, one slice each)
 hipError_t launch_encoder(int A, int C, int HE, int NHE, int mode, const EncoderArgs& a, int grid, hipStream_t s);
+int encoder_forward_grid(int64_t n, int cu_count);            // workgroups
 int encoder_backward_grid(int64_t n, int HE, int cu_count);   // workgroups, at most 2 per CU
 hipError_t launch_det_finish(int64_t count, const long long* acc, const unsigned int* absmax, int n, float* d_tex,
                              hipStream_t s);

@@ -660,7 +660,7 @@ def bench_train(nam, torch, wl, ctx, steps=20, warmup=3, with_oracle=False):
              "backward_and_scatter_ms": t_lb - t_fwd, "adam_ms": t_adam, "step_ms": ms,
              "deterministic_loss_backward_ms": t_det}
     # a decoder with two learned shading frames (28-64-64-64-3, Sec. 4.2) on the same batch: loss
-    # and gradients of the frame layer, decoder and texels (vector training kernel)
+    # and gradients of the frame layer, decoder and texels
     rf = wl.rngs(77)
     fdims = [m.channels + 12] + list(m.dims[1:])
     fdec = wl.xavier_mlp(rf[1], fdims).astype(np.float32)

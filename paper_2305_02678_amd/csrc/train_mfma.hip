@@ -564,12 +564,9 @@ __device__ __forceinline__ void put_pair(half8& v, int e, half2_t p) {
     v[e + 1] = p[1];
 }
 
-// 0xffff for the halves above zero (they are zero or more).  In asm, as the compiler takes the shifts
-// apart into a comparison and a selection per half.
+// 0xffff for the halves above zero (they are zero or more, so no sum carries into the upper half).
 __device__ __forceinline__ uint32_t half_mask(half2_t of) {
-    uint32_t m;
-    asm("v_pk_sub_i16 %0, 0, %1\n\tv_pk_ashrrev_i16 %0, 15, %0 op_sel_hi:[0,1]" : "=&v"(m) : "v"(half2_bits(of)));
-    return m;
+    return (((half2_bits(of) + 0x7fff7fffu) >> 15) & 0x00010001u) * 0xffffu;
 }
 __device__ __forceinline__ half2_t mask_half(half2_t v, uint32_t m) { return __builtin_bit_cast(half2_t, half2_bits(v) & m); }
 
@@ -1363,7 +1360,7 @@ struct alignas(16) TmSmem {
 // what it could), and with a texture the atomics, 412 us of lines by themselves.  More waves do not fit:
 // the gradients of a back wave take 176 registers, the activations of a front wave 96, two waves per SIMD
 // have 256 each.  Measured on 2^20 samples against FP32 matrix products in the same pairs: given codes
-// 611 -> 356 us, with fetch and scatter 770 -> 468 us (scattered by the front wave 664 us); 250,007
+// 611 -> 362 us, with fetch and scatter 770 -> 470 us (scattered by the front wave 664 us); 250,007
 // samples with two frames 250 -> 205 us.
 template <int C, int H, int NH, int NF>
 __global__ void __launch_bounds__(kTMThreads, 1) train_mfma_kernel(const TrainArgs a) {

@@ -472,9 +472,11 @@ nam_status nam_server_wait_all(nam_server* server);
 nam_status nam_server_stats(nam_server* server, nam_server_stats_t* out);
 
 /* Tiles per grouped launch, 1 to 8 (default 8).  Tiles with device buffers whose materials share
- * one matrix-core kernel (same shape, precision, address mode and frame presence) are taken
- * from the pending requests in arrival order and decoded by one launch, the persistent grid
- * shared among them by size; 1 launches every tile on its own.  Results do not change. */
+ * one matrix-core kernel (same shape, precision, address mode and frame presence) are decoded by
+ * one launch, the persistent grid shared among them by size: tiles of the oldest pending request
+ * and, in arrival order, of the 31 behind it, past those of other kernels (which keep their place:
+ * every launch starts with the oldest request); 1 launches every tile on its own.  Results do not
+ * change. */
 nam_status nam_server_set_group(nam_server* server, int max_tiles);
 /* Clear statistics, forget finished requests (their tickets become unknown) and restart the
  * epoch of replayed arrival times. */

@@ -9,9 +9,10 @@
 // the HBM budget before it is
 // launched and returns them when its completion event fires.  Tiles with device buffers whose
 // materials share one matrix-core kernel (same shape and output width, precision, address mode
-// and frame presence) are launched together, up to 8 in one grouped launch, taken in arrival order
-// (the grouped launch across resident materials: one launch instead of one per tile); a request whose tiles cannot
-// all be staged waits (admission by memory footprint).  Requests with host buffers are
+// and frame presence) are launched together, up to 8 in one grouped launch (across resident
+// materials: one launch instead of one per tile), those of the oldest request and, in arrival order, of
+// the next ones in line, past requests of other kernels; a request whose tiles cannot all be staged
+// waits (admission by memory footprint).  Requests with host buffers are
 // staged through a device arena carved from the budget; requests with device buffers only
 // reserve their bytes.  The decode kernel depends only on the material and its precision,
 // never on how requests are tiled or mixed, so each result is bitwise the same alone and in
@@ -98,6 +99,8 @@ struct Request {
     Clock::time_point completion;
     int64_t next = 0;        // first query not yet launched
     int64_t finished = 0;    // queries whose tiles completed
+    int on_device = 0;       // tiles in flight
+    bool forgotten = false;  // by a reset, with tiles in flight: freed when the last of them ends
     int state = 0;           // 0 queued, 1 running, 2 done, 3 failed, 4 cancelled
     nam_status error = NAM_OK;
 };
@@ -163,10 +166,19 @@ struct nam_server {
 
 namespace {
 
+// The line (`pending`) holds requests with queries left to launch and no others: whatever launches the
+// last of them, fails or cancels one takes it out at once, wherever it stands (a grouped launch reaches
+// past requests of other kernels), so that a request is never found there after its end.
+void leave_line(nam_server* s, Request* r) {
+    const auto it = std::find(s->pending.begin(), s->pending.end(), r);   // near the front
+    if (it != s->pending.end()) s->pending.erase(it);
+}
+
 void fail_request(nam_server* s, Request* r) {
     if (r->state != 3) s->failed += 1;
     r->state = 3;
     r->error = NAM_E_HIP;
+    leave_line(s, r);
 }
 
 // After a launch: how many distinct requests and launches are on the device now.
@@ -225,6 +237,7 @@ bool launch_tile(nam_server* s, Request* r, int si, int64_t cnt, Tile* t) {
     s->launches += 1;
     s->tiles += 1;
     r->next += cnt;
+    r->on_device += 1;
     r->state = 1;
     return true;
 }
@@ -248,7 +261,6 @@ int launch_group(nam_server* s, int si) {
     const int limit = std::min(kG, s->max_group);
     for (size_t k = 0; k < s->pending.size() && k < kLookAhead && count < limit; ++k) {
         Request* r = s->pending[k];
-        if (r->state >= 2 || r->next >= r->n) continue;
         const nam_material* m = s->materials[r->material];
         if (r->host_io || !nam::mfma_same_kernel(m0, m)) continue;
         int64_t next = r->next;
@@ -295,7 +307,9 @@ int launch_group(nam_server* s, int si) {
     for (int j = 0; j < count; ++j) {
         tiles[j].done = s->events[si];
         tiles[j].r->next = tiles[j].off + tiles[j].cnt;
+        tiles[j].r->on_device += 1;
         tiles[j].r->state = 1;
+        if (tiles[j].r->next >= tiles[j].r->n) leave_line(s, tiles[j].r);
         s->inflight.push_back(tiles[j]);
     }
     s->reserved += total;
@@ -376,6 +390,8 @@ void worker_loop(nam_server* s) {
             r->finished += t.cnt;
             if (r->finished == r->n && r->state == 1) finish_request(s, r, Clock::now());
             if (r->state >= 2) s->done_cv.notify_all();
+            r->on_device -= 1;
+            if (r->forgotten && r->on_device == 0) delete r;
             s->inflight[i] = s->inflight.back();
             s->inflight.pop_back();
             progressed = true;
@@ -384,14 +400,11 @@ void worker_loop(nam_server* s) {
         // budget blocks the ones behind it (arrival-order admission)
         for (int si = 0; si < (int)s->streams.size(); ++si) {
             if (s->stream_busy[si]) continue;
-            while (!s->pending.empty() && (s->pending.front()->state >= 2 || s->pending.front()->next >= s->pending.front()->n))
-                s->pending.pop_front();
             if (s->pending.empty()) break;
             Request* r = s->pending.front();
             if (!r->host_io && s->max_group > 1 && s->materials[r->material]->wprec != NAM_F32) {
                 const int got = launch_group(s, si);
                 if (got < 0) {
-                    while (!s->pending.empty() && s->pending.front()->state == 3) s->pending.pop_front();
                     s->done_cv.notify_all();
                     progressed = true;
                     continue;
@@ -404,7 +417,6 @@ void worker_loop(nam_server* s) {
             Tile t;
             if (!launch_tile(s, r, si, cnt, &t)) {
                 if (r->state == 3) {
-                    s->pending.pop_front();
                     s->done_cv.notify_all();
                     continue;
                 }
@@ -413,7 +425,7 @@ void worker_loop(nam_server* s) {
             s->inflight.push_back(t);
             note_on_device(s);
             progressed = true;
-            if (r->next >= r->n) s->pending.pop_front();
+            if (r->next >= r->n) leave_line(s, r);
         }
         if (s->stop && s->inflight.empty() && s->pending.empty() && s->arrivals.empty()) break;
         if (!progressed) {
@@ -560,7 +572,7 @@ nam_status nam_server_cancel(nam_server* s, uint64_t ticket) {
     if (r->state != 0 || r->next > 0) return set_error(NAM_E_BUSY, "request already started");
     for (auto a = s->arrivals.begin(); a != s->arrivals.end(); ++a)
         if (a->second == r) { s->arrivals.erase(a); break; }
-    s->pending.erase(std::remove(s->pending.begin(), s->pending.end(), r), s->pending.end());
+    leave_line(s, r);
     r->state = 4;
     s->done_cv.notify_all();
     return NAM_OK;
@@ -630,8 +642,10 @@ nam_status nam_server_reset_stats(nam_server* s) {
     s->peak_launches_on_device = 0;
     for (auto it = s->requests.begin(); it != s->requests.end();) {
         if (it->second->state >= 2) {
-            if (it->second->state == 3) s->failed -= 1;
-            delete it->second;
+            Request* r = it->second;
+            if (r->state == 3) s->failed -= 1;
+            r->forgotten = true;                  // a failed one may have tiles in flight
+            if (r->on_device == 0) delete r;
             it = s->requests.erase(it);
         } else {
             ++it;

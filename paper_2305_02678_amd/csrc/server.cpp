@@ -332,13 +332,16 @@ void finish_request(nam_server* s, Request* r, Clock::time_point now) {
 }
 
 // Takes the inbox over (mu held): the requests become known, those without queries are done, the
-// others wait for their arrival time.
-void drain(nam_server* s) {
+// others wait for their arrival time.  A worker asleep on an empty inbox computed its waking time before
+// these arrivals, so anyone else who takes requests over wakes it.
+void drain(nam_server* s, bool worker = false) {
     std::vector<Request*> got;
     {
         std::lock_guard<std::mutex> g(s->in_mu);
         got.swap(s->inbox);
+        if (!worker && !got.empty()) s->wake = true;
     }
+    if (!worker && !got.empty()) s->in_cv.notify_one();
     for (Request* r : got) {
         s->requests[r->ticket] = r;
         if (r->n == 0) finish_request(s, r, r->arrival);
@@ -358,7 +361,7 @@ void worker_loop(nam_server* s) {
     (void)hipSetDevice(s->ctx->device);
     std::unique_lock<std::mutex> lk(s->mu);
     while (true) {
-        drain(s);
+        drain(s, true);
         const Clock::time_point now = Clock::now();
         // arrivals whose time has come
         while (!s->arrivals.empty() && s->arrivals.begin()->first <= now) {

@@ -233,6 +233,25 @@ void reset_with_tile_of_failed_request() {
     }
 }
 
+// A client that submits to an idle server and asks until the request is done: whatever takes the
+// submission over from the inbox, the worker hears of it.
+void poll_from_idle() {
+    Fixture f(2, {16});
+    constexpr int kTimes = 200;
+    double sum = 0.0;
+    for (int i = 0; i < kTimes; ++i) {
+        std::this_thread::sleep_for(std::chrono::milliseconds(1));            // the worker sleeps
+        const auto t0 = Clock::now();
+        const uint64_t t = f.submit(0, kTile);
+        nam_server_stats_t st;
+        if (i % 2) CHECK(nam_server_stats(f.s, &st) == NAM_OK);
+        CHECK(f.finishes(t));
+        sum += std::chrono::duration<double>(Clock::now() - t0).count();
+    }
+    std::printf("mean %.1f us\n", sum / kTimes * 1e6);
+    CHECK(sum / kTimes < 500e-6);                                             // it sleeps for 2 ms at a time
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -240,6 +259,7 @@ int main(int argc, char** argv) {
     if (what == "reset_behind_other_kernel") reset_behind_other_kernel();
     else if (what == "reset_after_failed_group") reset_after_failed_group();
     else if (what == "reset_with_tile_of_failed_request") reset_with_tile_of_failed_request();
+    else if (what == "poll_from_idle") poll_from_idle();
     else return 2;
     std::printf("%s: done\n", what.c_str());
     return 0;

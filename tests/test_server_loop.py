@@ -1,6 +1,6 @@
 """The request loop (csrc/server.cpp) built for the host with its launches replaced by events that
 end when the scenario says so (native/server_loop.cpp), under the address sanitizer: requests that
-finish out of line, a reset while others run, launches that fail."""
+finish out of line, a reset while others run, launches that fail, a client that polls."""
 import os
 import shutil
 import subprocess
@@ -35,3 +35,7 @@ def _run(program, scenario):
                                       "reset_with_tile_of_failed_request"])
 def test_reset_while_requests_run(program, scenario):
     _run(program, scenario)
+
+
+def test_submissions_reach_an_idle_worker(program):
+    _run(program, "poll_from_idle")

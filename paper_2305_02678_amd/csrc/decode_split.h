@@ -84,9 +84,11 @@ __device__ __forceinline__ float relu_twice(float x) { return x + fabsf(x); }
 // argument split at its nearest integer, f in two steps (the second adds the low part of log2 e);
 // log1p(e) = 2 atanh(s), s = e / (2 + e) <= 1/3, by the series in s^2 (the first term left out is
 // below 2^-27 of the sum), with the quotient's remainder, that of the rounded 2 + e included, added
-// to the small terms.
+// to the small terms.  Past |q| = 128, where e is below every FP32 number, x stays -128: the split of a
+// larger argument would leave more in f than exp2 takes.  A NaN stays.  Below 2^-25 the result is e, also
+// where halving it would round (subnormal).
 __device__ __forceinline__ float softplus_split(float q) {
-    const float x = -fabsf(q);
+    const float x = fabsf(q) > 128.0f ? -128.0f : -fabsf(q);
     const float i = __builtin_rintf(x * 1.44269502162933349609375f);
     float f = fmaf(x, 1.44269502162933349609375f, -i);
     f = fmaf(x, 1.92596299e-8f, f);
@@ -102,7 +104,8 @@ __device__ __forceinline__ float softplus_split(float q) {
     p = fmaf(p, t, 2.0f / 7.0f);
     p = fmaf(p, t, 2.0f / 5.0f);
     p = fmaf(p, t, 2.0f / 3.0f);
-    return fmaxf(q, 0.0f) + fmaf(2.0f, s, fmaf(s * t, p, 2.0f * sl));
+    const float l = fmaf(2.0f, s, fmaf(s * t, p, 2.0f * sl));
+    return fmaxf(q, 0.0f) + (e < 0x1p-25f ? e : l);
 }
 
 // Parts of a weight: high and low half, and where a third is kept what those two leave (a weight's

@@ -117,3 +117,19 @@ def test_values_without_scales_keep_the_fp32_kernels(nam, ctx, torch):
     m.params[-1] = np.inf                               # the last bias
     got = nam.decode(nam.Material.from_workload(ctx, m), *nam.to_device(q)).cpu().numpy()
     assert np.isinf(got[:, 2]).all() and np.isfinite(got[:, :2]).all()
+
+
+@pytest.mark.parametrize("C,H,NH,nf,albedo", [(16, 64, 3, 0, False), (8, 32, 2, 2, True)])
+@pytest.mark.parametrize("size", [100.0, 130.0, 1.23e10, 3e11, 1e20, 1e30])
+def test_output_biases_of_any_size(nam, ctx, torch, C, H, NH, nf, albedo, size):
+    """softplus far from zero: q itself above (to the few roundings of its sum), nothing below, where
+    exp(q) is the smallest FP32 numbers (half a step of 2^-149) or under them."""
+    r = wl.rngs(74)
+    m = wl.make_material(r[0], r[1], 32, 32, C, 4, [H] * NH, n_frames=nf, albedo=albedo)
+    m.params[-3:] = np.float32([size, -size, size])
+    q = wl.uniform_queries(r[2], 300, -0.5, 3.5)
+    ref = _reference(m, q, None)
+    got = nam.decode(nam.Material.from_workload(ctx, m), *nam.to_device(q)).cpu().numpy().astype(np.float64)
+    rows = slice(got.shape[1] - 3, None)
+    rel = 1e-5 * np.maximum(1.0, _partial_sums(m, q)[rows])
+    assert (np.abs(got - ref)[:, rows] <= np.where(ref[:, rows] > 1.0, 1e-6, rel) * ref[:, rows] + 2.0 ** -150).all()

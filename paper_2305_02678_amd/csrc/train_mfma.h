@@ -14,11 +14,15 @@
 // Arithmetic.  FP32 matrix instructions and vector instructions take turns on a SIMD, so products of
 // FP32 factors run on the FP16 matrix cores, each factor split into two FP16 halves as in the split
 // decode (decode_split.h).  Weights have a power of two per layer (AW); the values of a sample have one
-// per layer, from their own largest magnitude, which puts it in [2^11, 2^12): nothing overflows, and
+// per layer, from their own largest magnitude, which puts it in [2^14, 2^15): nothing overflows, and
 // samples of any scale keep their 22 bits beside each other.  In a weight gradient, a sum over
 // samples, every sample's inputs are multiplied by the power of two that brings its product to the
-// scale 2^x of the accumulators (exact, or lost far below them); x is the smallest exponent the wave
-// has met, and the back wave rescales its accumulators when it falls.
+// scale 2^x of the accumulators; x follows the samples, and the back wave rescales its accumulators when
+// it changes.  The factor is applied in FP16 and so not below 2^-12 (kFarStep): an input's low half
+// keeps its bits down to 2^-5 of the sample's largest there, and loses 2^-28 of the largest below.  A
+// sample further down would lose bits, or all of itself, also in the rows that no large sample touches
+// (its inactive neurons'), so a tile whose samples span more than that hands the layer over once more
+// for each 12 powers of two, with those samples alone and an x that is larger by as many.
 //
 // ReLUs.  A unit within rounding of its kink would fall on a side that depends on the arithmetic, and
 // with it a sample's whole gradient.  A tile with such a unit (a pre-activation below 2^-19 of its
@@ -88,10 +92,12 @@ struct TmSlot {
     uint8_t delta[kSlotMatrix];
     uint8_t input[kSlotMatrix];
 };
-struct TmSlotScale {
+struct alignas(16) TmSlotScale {
     _Float16 bias_weight[16];
     int x, xb;                    // weight gradients are summed times 2^x, bias gradients times 2^xb
+    int more;                     // the same layer of the same tile follows, with smaller samples
 };
+constexpr int kFarStep = 12, kFarSteps = 5;
 
 // The decoder's operand blocks: FP32 blocks of the exact forward (read from memory by the forward
 // kernel and by tiles that need it), then the part that the training kernel keeps in LDS.  Offsets in

@@ -501,7 +501,8 @@ struct alignas(16) TmScatter {
 // The slots of one pair: handoff n lies in slot n & 1.  `filled` counts the handoffs written by the
 // front wave, `emptied` those the back wave has read; each is written by one wave only.  The front
 // wave waits until handoff n - 2 is read, the back wave until handoff n is written.  Both waves of a
-// pair walk the same tiles with the same number of handoffs each, so every wait ends.
+// pair walk the same tiles with the same number of handoffs each (`more` tells of a repeated one), so
+// every wait ends.
 typedef __attribute__((address_space(3))) volatile int lds_count;
 
 struct TmRing {
@@ -544,8 +545,8 @@ __device__ __forceinline__ float sample_max(float m) {
     return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
-// Exponent e with 2^e times a sample's largest magnitude m in [2^11, 2^12), as far as 2^e is a float.
-__device__ __forceinline__ int half_exponent(float m) { return min(12 - __builtin_amdgcn_frexp_expf(m), 126); }
+// Exponent e with 2^e times a sample's largest magnitude m in [2^14, 2^15), as far as 2^e is a float.
+__device__ __forceinline__ int half_exponent(float m) { return min(15 - __builtin_amdgcn_frexp_expf(m), 126); }
 
 __device__ __forceinline__ float pow2(int e) { return ldexpf(1.0f, e); }
 
@@ -708,47 +709,91 @@ __device__ __forceinline__ void tm_range(const floatx4* acc, float& most, float&
         }
 }
 
+// The exponent x that a layer's sums have in the back wave (times 2^x), and the least it has had: sums
+// that were taken there, of up to 2^50, are still floats 2^(kFarStep kFarSteps) above.
+struct TmScale {
+    int x = kNoSample, least = kNoSample;
+
+    __device__ __forceinline__ int room() const { return (least - x) / kFarStep + kFarSteps; }   // steps above x
+    // Step of a sample of exponent e: its factor 2^(x + step kFarStep - e) is at most 1 and at least
+    // 2^-kFarStep, where the room suffices.
+    __device__ __forceinline__ int step(int e) const { return min(max(e - x - 1, 0) / kFarStep, room()); }
+    // Fits x to exponents from lo to hi: unchanged if step 0 does for all of them.
+    __device__ __forceinline__ void fit(int lo, int hi) {
+        if (lo < x || hi > x + kFarStep) x = min(lo, least + kFarStep * kFarSteps);
+        least = min(least, x);
+    }
+};
+
 // Hands one layer over: deltas (NT row tiles, halves, scale exponent ed per sample), inputs (NA column
-// tiles, halves, scale exponent ea).  x, xb: the wave's running exponents of this layer's weight and
-// bias gradients.  The caller ends the fill, with other work between the writes and that wait.
+// tiles, halves, scale exponent ea).  xw, xb: scales of the sums of this layer's weight and bias
+// gradients.  They follow the tile; one whose samples span more than kFarStep goes in several handoffs,
+// with the factors of all but a step's samples zero.  The caller ends the last fill, with other work
+// between the writes and that wait.
 template <int NT, int NA>
 __device__ __forceinline__ void tm_handoff(TmRing& ring, const half2_t (*dh)[2], const half2_t (*dl)[2], int ed,
-                                           const half2_t (*ah)[2], const half2_t (*al)[2], int ea, int& x, int& xb,
+                                           const half2_t (*ah)[2], const half2_t (*al)[2], int ea, TmScale& xw, TmScale& xb,
                                            float sign, int lane) {
     const int g = lane >> 4, s = lane & 15;
-    const int emptied = ring.peek_emptied();
-    const auto lower = [](int& run, int e) {
-        if (__builtin_amdgcn_ballot_w64(e < run)) {           // uniform, rare
-            int m = e;
+    int emptied = ring.peek_emptied();
+    const bool sample = ed < kNoSample / 2;
+    const int e = ed + ea;
+    int last = 0;
+    const bool fits = !sample || max((unsigned)(e - xw.x), (unsigned)(ed - xb.x)) <= (unsigned)kFarStep;
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!fits) != 0, 0)) {
+        const auto over_samples = [&](int m, auto pick) {                 // uniform, rare
             #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) m = min(m, __shfl_xor(m, o, 64));
-            run = min(run, __builtin_amdgcn_readfirstlane(m));
-        }
-    };
-    lower(x, ed + ea);
-    lower(xb, ed);
-    const _Float16 f = (_Float16)(sign * pow2(x - ed - ea));           // at most 1; 0 far below the accumulators
-    const half2_t f2 = {f, f};
-    ring.begin_fill(emptied);
-    TmSlot* m = ring.slot();
-    TmSlotScale* sc = ring.scale();
-    if (g == 0) sc->bias_weight[s] = (_Float16)(sign * pow2(xb - ed));
-    if (lane == 0) {
-        sc->x = x;
-        sc->xb = xb;
+            for (int o = 8; o > 0; o >>= 1) m = pick(m, __shfl_xor(m, o, 64));
+            return __builtin_amdgcn_readfirstlane(m);
+        };
+        const auto fit = [&](TmScale& to, int of) {
+            const int lo = over_samples(sample ? of : kNoSample, [](int a, int b) { return a < b ? a : b; });
+            const int hi = over_samples(sample ? of : -kNoSample, [](int a, int b) { return a < b ? b : a; });
+            to.fit(lo, hi);
+            return to.step(hi);
+        };
+        last = fit(xw, e);
+        last = max(last, fit(xb, ed));
     }
-    const auto store = [](uint8_t* p, half2_t a, half2_t b) { *reinterpret_cast<uint2*>(p) = make_uint2(half2_bits(a), half2_bits(b)); };
-    #pragma unroll
-    for (int t = 0; t < (NT > NA ? NT : NA); ++t) {
-        const int at = slot_group(s, 4 * t + g);
-        if (t < NT) {
-            store(m->delta + at, dh[t][0], dh[t][1]);
-            store(m->delta + kPlane + at, dl[t][0], dl[t][1]);
+    for (int k = 0;; ++k) {
+        // at most 1; 0 for no sample
+        float fw = sample ? pow2(xw.x - e) : 0.0f, fb = sample ? pow2(xb.x - ed) : 0.0f;
+        int x = xw.x, b = xb.x;
+        if (__builtin_expect(last > 0, 0)) {                              // uniform, rarer
+            TmScale w = xw, v = xb;
+            asm volatile("" : "+s"(w.x), "+s"(v.x));                      // nothing of this ahead of the branch
+            x = w.x + min(k, w.room()) * kFarStep;
+            b = v.x + min(k, v.room()) * kFarStep;
+            fw = sample && w.step(e) == k ? pow2(x - e) : 0.0f;
+            fb = sample && v.step(ed) == k ? pow2(b - ed) : 0.0f;
         }
-        if (t < NA) {
-            store(m->input + at, ah[t][0] * f2, ah[t][1] * f2);
-            store(m->input + kPlane + at, al[t][0] * f2, al[t][1] * f2);
+        const _Float16 f = (_Float16)(sign * fw);
+        const half2_t f2 = {f, f};
+        ring.begin_fill(emptied);
+        TmSlot* m = ring.slot();
+        TmSlotScale* sc = ring.scale();
+        if (g == 0) sc->bias_weight[s] = (_Float16)(sign * fb);
+        if (lane == 0) {
+            sc->x = x;
+            sc->xb = b;
+            sc->more = last - k;
         }
+        const auto store = [](uint8_t* p, half2_t a, half2_t b) { *reinterpret_cast<uint2*>(p) = make_uint2(half2_bits(a), half2_bits(b)); };
+        #pragma unroll
+        for (int t = 0; t < (NT > NA ? NT : NA); ++t) {
+            const int at = slot_group(s, 4 * t + g);
+            if (t < NT) {
+                store(m->delta + at, dh[t][0], dh[t][1]);
+                store(m->delta + kPlane + at, dl[t][0], dl[t][1]);
+            }
+            if (t < NA) {
+                store(m->input + at, ah[t][0] * f2, ah[t][1] * f2);
+                store(m->input + kPlane + at, al[t][0] * f2, al[t][1] * f2);
+            }
+        }
+        if (__builtin_expect(k == last, 1)) break;
+        ring.end_fill();
+        emptied = ring.peek_emptied();
     }
 }
 
@@ -782,10 +827,8 @@ __device__ __forceinline__ void train_front(const TrainArgs& a, const float* lds
     // over many samples would keep.  Odd samples' deltas therefore run through the backward pass with
     // the other sign, and odd waves sum their gradients with the other sign (TmGradient::weight).
     const float sign = (s & 1) ? -1.0f : 1.0f, back_sign = (wid & 1) ? -sign : sign;
-    // running exponents of the gradients of layers 1..NH, the output layer and the frame layer
-    int x[NH + 3], xb[NH + 3];
-    #pragma unroll
-    for (int k = 0; k < NH + 3; ++k) x[k] = xb[k] = kNoSample;
+    // scales of the gradients of layers 1..NH, the output layer and the frame layer
+    TmScale x[NH + 3], xb[NH + 3];
     TmQuery q;
     TmFetch cur, nxt;
     if (wid < tiles) {
@@ -1160,8 +1203,11 @@ struct TmGradient {
         x = xb = 0;
     }
 
-    // Adds the layer's handoff.
+    // Adds the layer's handoffs of a tile.
     __device__ __forceinline__ void add(TmRing& ring) {
+        while (add_one(ring)) {}
+    }
+    __device__ __forceinline__ bool add_one(TmRing& ring) {
         typedef __fp16 fp16x4 __attribute__((ext_vector_type(4)));
         typedef __attribute__((address_space(3))) fp16x4 lds_fp16x4;
         const int lane = fresh_lane(), g = lane >> 4, j = lane & 15;
@@ -1185,7 +1231,8 @@ struct TmGradient {
         dl[0] = read(m->delta + kPlane, 0);
         const half4 bw = *reinterpret_cast<const half4*>(&sc->bias_weight[4 * g]);
         const int nx = __builtin_amdgcn_readfirstlane(sc->x), nb = __builtin_amdgcn_readfirstlane(sc->xb);
-        if (nx != x || nb != xb) {               // uniform, rare: the exponents fell
+        const bool more = __builtin_amdgcn_readfirstlane(sc->more) != 0;
+        if (nx != x || nb != xb) {               // uniform, rare: the exponents changed
             #pragma unroll
             for (int t = 0; t < RT; ++t) {
                 #pragma unroll
@@ -1218,6 +1265,7 @@ struct TmGradient {
             b[t] = __builtin_amdgcn_fdot2(half2_t{h[2], h[3]}, b1, b[t], false);
         }
         ring.end_read();
+        return more;
     }
 
     // sign: the wave's

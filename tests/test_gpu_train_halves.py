@@ -8,6 +8,8 @@ nothing), so that every ReLU is on the same side in FP64.  Tolerances: a pair of
 a sample's largest value, so each of the at most nine products in a row is within 2^-21 of it times the
 root of 64 terms at worst, 3e-5 together, for one sample's gradient; sums over samples of independent
 errors of 2^-24 stay within 1e-6 of their norm, where a bias of 1/5 of that would reach 3e-6 at 65,536.
+A sample far above the others takes no bits from the gradients that it does not touch itself: these are
+held to the bound of one sample's gradient on their own norm, row by row.
 """
 import numpy as np
 import pytest
@@ -88,3 +90,31 @@ def test_sums_over_either_sign(nam, torch, C, hidden):
     q.uv[~keep.numpy()] = np.nan
     gp = model.backward(tex, par, *nam.to_device(q), d_rgb.cuda())[1]
     assert (gp.cpu().double() - dp).norm() <= 1e-6 * dp.norm()
+
+
+@pytest.mark.parametrize("C,hidden", [(16, [64] * 3), (8, [32] * 2), (16, [16] * 2), (8, [64])])
+@pytest.mark.parametrize("n", [16, 65536])
+@pytest.mark.parametrize("above", [10, 16, 24, 30, 50, 70])
+def test_small_samples_beside_large_ones(nam, torch, C, hidden, n, above):
+    """Output gradients of order 1, but for one sample of a tile (n = 16), or one of the first tile of
+    every wave: 2^above, in the first output alone."""
+    model, tex, par, q, z, keep, net, p64 = _case(torch, nam, C, hidden, n, 95)
+    d_rgb = torch.from_numpy(np.random.default_rng(96).standard_normal((n, 3)).astype(np.float32))
+    large = torch.zeros(n, dtype=torch.bool)
+    large[3:16 * 1024:16] = True                         # at most 256 CUs of 4 pairs of waves
+    d_rgb[large] = torch.tensor([2.0 ** above, 0.0, 0.0])
+    dp, = torch.autograd.grad((net(z.double())[0] * torch.where(keep[:, None], d_rgb.double(), 0.0)).sum(), p64, retain_graph=True)
+    q.uv[~keep.numpy()] = np.nan
+    gp = model.backward(tex, par, *nam.to_device(q), d_rgb.cuda())[1].cpu().double()
+    # what the large samples touch: their share of the gradient is not zero
+    share, = torch.autograd.grad((net(z.double())[0] * torch.where((keep & large)[:, None], d_rgb.double(), 0.0)).sum(), p64)
+    o, rows = 0, 0
+    dims = [C + 6] + hidden + [3]
+    for a, b in zip(dims[:-1], dims[1:]):
+        for r in range(b):
+            row = torch.cat([torch.arange(o + r * a, o + (r + 1) * a), torch.tensor([o + a * b + r])])
+            if (share[row] == 0).all() and (dp[row] != 0).any():
+                rows += 1
+                assert (gp[row] - dp[row]).norm() <= 3e-5 * dp[row].norm(), (a, b, r)
+        o += a * b + b
+    assert rows >= (2 if n > 16 else 10)

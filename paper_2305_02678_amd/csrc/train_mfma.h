@@ -26,13 +26,19 @@
 //
 // ReLUs.  A unit within rounding of its kink would fall on a side that depends on the arithmetic, and
 // with it a sample's whole gradient.  A tile with such a unit (a pre-activation below 2^-19 of its
-// sample's largest one in the layer, some twenty times the differences measured; about 1% of tiles),
-// or whose output is not finite, runs its forward pass again in FP32 (v_mfma_f32_16x16x4_f32) and takes
-// activations and outputs from there: no ReLU changes side.  Those FP32 sums have a fixed order.  Slot
-// 4g + r of an accumulator's row tile holds neuron 4g + r or, in natural order, neuron 4r + g: then the
-// K steps run over the neurons in ascending order, and as the instruction is a chain of four FMAs in
-// ascending k, the sums are bit for bit those of the vector kernel (train_vec.h), whose shapes (learned
-// frames, width 16, 1 or 4 hidden layers) keep that order.
+// sample's largest one in the layer; about 1% of tiles), or whose output is not finite, runs its forward
+// pass again in FP32 (v_mfma_f32_16x16x4_f32) and takes activations and outputs from there.  The margin
+// is a measured one: over 7 million units of random decoders the two arithmetics differ by 2^-20.4 of
+// that largest one at most, mostly by 2^-23, and a ReLU changes side only where a rare difference meets a
+// pre-activation smaller than itself; inputs that cancel to pre-activations far below their products may
+// exceed it.  A unit without weights and bias (pruned, or not yet trained) is 0 in either arithmetic: its
+// packed bias is NaN, which the comparisons pass over and the ReLU turns into its 0, so such units send
+// no tile the long way.  An infinite weight sends all of them there.
+//
+// The FP32 sums have a fixed order.  Slot 4g + r of an accumulator's row tile holds neuron 4g + r or, in
+// natural order, neuron 4r + g: then the K steps run over the neurons in ascending order, and as the
+// instruction is a chain of four FMAs in ascending k, the sums are bit for bit those of the vector kernel
+// (train_vec.h), whose shapes (learned frames, width 16, 1 or 4 hidden layers) keep that order.
 //
 // Layouts.  Lane (g, s) = (lane / 16, lane % 16) works on sample s of the tile.  A layer is Y = W X with
 // the weights as the A operand (16 output rows per row tile) and one sample per column; its
@@ -126,7 +132,7 @@ struct TrainLayout {
     static constexpr int FFB = FF + (NF > 0 ? C / 4 * 64 : 0);     // its biases
     static constexpr int FWD = FFB + (NF > 0 ? 16 : 0);            // end of the forward kernel's part
     static constexpr int BF = FWD;                                 // frame layer transposed: [q][lane]
-    static constexpr int AW = BF + (NF > 0 ? 3 * 64 : 0);          // exponents of the layers' weight scales
+    static constexpr int AW = BF + (NF > 0 ? 3 * 64 : 0);          // exponents of the layers' weight scales (kNoExponent)
     static constexpr int BLOCKS = AW + 8;                          // blocks of halves
     static constexpr int A1 = BLOCKS;                              // [j][3 parts][256]
     static constexpr int AH = A1 + HT * 3 * 256;                   // [k][j][s][P][256]

@@ -31,6 +31,18 @@ __device__ __forceinline__ float tm_logistic(float q) {
 __device__ __forceinline__ f32x4 ld4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
 __device__ __forceinline__ void st4(float* p, f32x4 v) { *reinterpret_cast<f32x4*>(p) = v; }
 
+__device__ __forceinline__ bool no_weights(const float* __restrict__ w, int count) {
+    bool none = true;
+    for (int j = 0; j < count && none; j += 16) {             // 16 loads under way
+        float v[16];
+        #pragma unroll
+        for (int c = 0; c < 16; ++c) v[c] = w[min(j + c, count - 1)];
+        #pragma unroll
+        for (int c = 0; c < 16; ++c) none = none && v[c] == 0.0f;
+    }
+    return none;
+}
+
 // FP32 blocks of TrainLayout (everything ahead of AW) from packed parameters, one thread per float.  p:
 // the decoder; fp: the frame layer (NF > 0).
 template <int C, int H, int NH, int NF>
@@ -57,7 +69,11 @@ __device__ __forceinline__ float packed_float(const float* __restrict__ p, const
         if (i < NO) return p[oo + i * H + 16 * t + nat(4 * (lane >> 4) + r)];
     } else if (e < L::FF) {
         const int x = e - L::BIAS, k = 1 + x / (HT * 16), y = x % (HT * 16);   // y = slot 16t + 4g + r
-        if (k <= NH) return p[param_off<IN, H>(k) + (k == 1 ? IN : H) * H + (y & ~15) + nat(y & 15)];
+        if (k <= NH) {
+            const int fi = k == 1 ? IN : H, o = (y & ~15) + nat(y & 15);
+            const float b = p[param_off<IN, H>(k) + fi * H + o];
+            return b == 0.0f && no_weights(p + param_off<IN, H>(k) + o * fi, fi) ? __builtin_nanf("") : b;
+        }
         if (y < NO) return p[oo + NO * H + y];
     } else if (e < L::FWD) {
         if (e < L::FFB) {
@@ -81,7 +97,9 @@ __host__ __device__ constexpr int split_input(int g, int e) {
     return d < 6 * (NF > 1 ? NF : 1) ? C + d : -1;
 }
 
-// Exponent that puts a layer's largest weight in [2^9, 2^10) (0 for a layer of zeros); one wave.
+// Exponent that puts a layer's largest weight in [2^9, 2^10) (0 for a layer of zeros); one wave.  With an
+// infinite weight there is none: every tile's forward pass runs in FP32.
+constexpr int kNoExponent = 1000;
 __device__ __forceinline__ int weight_exponent(const float* __restrict__ w, int count, int lane) {
     float m = 0.0f;
     for (int i = lane; i < count; i += 16 * 64) {             // 16 loads under way
@@ -92,7 +110,8 @@ __device__ __forceinline__ int weight_exponent(const float* __restrict__ w, int 
         for (int j = 0; j < 16; ++j) m = fmaxf(m, fabsf(v[j]));
     }
     for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-    return m > 0.0f && __builtin_isfinite(m) ? min(max(10 - __builtin_amdgcn_frexp_expf(m), -100), 100) : 0;
+    if (!__builtin_isfinite(m)) return kNoExponent;
+    return m > 0.0f ? min(max(10 - __builtin_amdgcn_frexp_expf(m), -100), 100) : 0;
 }
 
 // Packs a decoder: workgroups [0, nf) write the FP32 blocks, a wave of the later ones one block of
@@ -121,6 +140,7 @@ __global__ void __launch_bounds__(256) pack_train_kernel(const float* __restrict
         float w[8];
         #pragma unroll
         for (int e = 0; e < 8; ++e) w[e] = e < halves ? v(e) : 0.0f;
+        if (aw == kNoExponent) aw = 0;
         #pragma unroll
         for (int e = 0; e < 8; ++e) {
             if (e >= halves) break;
@@ -550,6 +570,9 @@ __device__ __forceinline__ int half_exponent(float m) { return min(15 - __builti
 
 __device__ __forceinline__ float pow2(int e) { return ldexpf(1.0f, e); }
 
+// max(x, 0), 0 for NaN, in one instruction (a max takes two: one quiets NaNs).
+__device__ __forceinline__ float relu(float x) { return __builtin_amdgcn_fmed3f(x, 0.0f, __builtin_inff()); }
+
 // Sum exponents of a sample that adds nothing: above any other.
 constexpr int kNoSample = 1 << 20;
 
@@ -823,6 +846,12 @@ __device__ __forceinline__ void train_front(const TrainArgs& a, const float* lds
     int aw[NH + 2];
     #pragma unroll
     for (int k = 1; k <= NH + 1; ++k) aw[k] = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int*>(block(L::AW))[k]);
+    bool no_exponent = false;
+    #pragma unroll
+    for (int k = 1; k <= NH + 1; ++k) {
+        no_exponent = no_exponent || aw[k] == kNoExponent;
+        aw[k] = aw[k] == kNoExponent ? 0 : aw[k];
+    }
     // The matrix cores round the sums inside a product down, by a part of the last bit: a bias that a sum
     // over many samples would keep.  Odd samples' deltas therefore run through the backward pass with
     // the other sign, and odd waves sum their gradients with the other sign (TmGradient::weight).
@@ -875,7 +904,7 @@ __device__ __forceinline__ void train_front(const TrainArgs& a, const float* lds
         // ---- forward in halves
         TmHalves<KS> act[NH];
         int ea[NH];                              // 2^ea times an activation is in the halves
-        bool near = false;                       // a unit near its kink
+        bool near = no_exponent;                 // a unit near its kink
         f32x4 qo;
         {
             floatx4 acc[HT];
@@ -895,16 +924,16 @@ __device__ __forceinline__ void train_front(const TrainArgs& a, const float* lds
                 float most, least;
                 tm_range<HT>(acc, most, least);
                 const float m = sample_max(most);
-                near = near || least < m * 1.9073486328125e-6f;            // 2^-19
+                near = near || least < m * 0x1p-19f;
                 const int ec = half_exponent(m);
                 ea[k - 1] = ec + t0;
-                const float c = pow2(ec - 1);
+                const float c = pow2(ec);
                 #pragma unroll
                 for (int t = 0; t < 2 * KS; ++t)
                     #pragma unroll
                     for (int j = 0; j < 4; j += 2) {
                         half2_t h = {}, l = {};
-                        if (t < HT) split_pair(relu_twice(acc[t < HT ? t : 0][j]) * c, relu_twice(acc[t < HT ? t : 0][j + 1]) * c, one, h, l);
+                        if (t < HT) split_pair(relu(acc[t < HT ? t : 0][j]) * c, relu(acc[t < HT ? t : 0][j + 1]) * c, one, h, l);
                         put_pair(act[k - 1].h[t / 2], 4 * (t % 2) + j, h);
                         put_pair(act[k - 1].l[t / 2], 4 * (t % 2) + j, l);
                     }

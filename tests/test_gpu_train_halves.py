@@ -118,3 +118,56 @@ def test_small_samples_beside_large_ones(nam, torch, C, hidden, n, above):
                 assert (gp[row] - dp[row]).norm() <= 3e-5 * dp[row].norm(), (a, b, r)
         o += a * b + b
     assert rows >= (2 if n > 16 else 10)
+
+
+@pytest.mark.parametrize("C,hidden", [(16, [64] * 3), (8, [32] * 2), (16, [16] * 2)])
+def test_units_without_weights(nam, torch, C, hidden):
+    """A unit of every layer whose weights and bias are zero: no gradient through it, and the time of a
+    decoder without such units (no FP32 repeat of every tile's forward pass)."""
+    n = 1 << 18
+    model, _, par, q, z, _, _, _ = _case(torch, nam, C, hidden, n, 97)
+    unit, o, dims = [], 0, [C + 6] + hidden + [3]
+    for a, b in zip(dims[:-2], dims[1:-1]):
+        unit += [*range(o + 5 * a, o + 6 * a), o + a * b + 5]
+        o += a * b + b
+    small = par.clone()
+    small[unit] = 0.0
+    dev = [torch.from_numpy(np.ascontiguousarray(v, np.float32)).cuda() for v in (z.numpy(), q.wi, q.wo)]
+    target = torch.rand(n, 3, device="cuda")
+    times = []
+    for p in (par, small):
+        t = []
+        for _ in range(15):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            grad = model.loss_backward_codes(p, *dev, target)[2]
+            e[1].record()
+            torch.cuda.synchronize()
+            t.append(e[0].elapsed_time(e[1]))
+        times.append(sorted(t)[len(t) // 2])
+    print(f"{times[0]:.3f} ms, with units without weights {times[1]:.3f} ms", flush=True)
+    assert (grad[unit] == 0).all()
+    assert times[1] <= 1.15 * times[0]
+
+
+@pytest.mark.parametrize("C,hidden", [(16, [64] * 3), (8, [32] * 2), (16, [16] * 2)])
+def test_infinite_weight_of_an_inactive_unit(nam, torch, C, hidden):
+    """A weight of minus infinity on a direction that is always positive turns its unit off and leaves
+    loss and gradients finite: the same gradients as without the unit."""
+    n = 1000
+    model, _, par, q, z, _, _, _ = _case(torch, nam, C, hidden, n, 99)
+    a = C + 6
+    q.wo[:] = np.abs(q.wo) + np.float32(0.01)
+    dev = [torch.from_numpy(np.ascontiguousarray(v, np.float32)).cuda() for v in (z.numpy(), q.wi, q.wo)]
+    target = torch.rand(n, 3, device="cuda")
+    off = par.clone()
+    off[5 * a:6 * a] = 0.0
+    off[5 * a + C + 5] = float("-inf")
+    without = par.clone()
+    without[5 * a:6 * a] = 0.0
+    without[a * hidden[0] + 5] = -1.0
+    loss, dz, dp = model.loss_backward_codes(off, *dev, target)
+    loss1, dz1, dp1 = model.loss_backward_codes(without, *dev, target)
+    assert abs(float(loss) - float(loss1)) <= 1e-6 * float(loss1)
+    assert torch.isfinite(dz).all() and torch.isfinite(dp).all()
+    assert (dz - dz1).norm() <= 1e-6 * dz1.norm() and (dp - dp1).norm() <= 1e-6 * dp1.norm()

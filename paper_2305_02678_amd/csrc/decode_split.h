@@ -13,7 +13,8 @@
 // components are at most kSplitMaxDir no half can overflow, and the subnormal step of the low
 // half, propagated to the output, stays below the FP32 rounding there.  A material that has no
 // such scales (non-finite or extreme values) keeps the FP32 kernels; a query with larger or
-// non-finite directions is decoded in FP32 on the vector ALU by the wave that finds it.
+// non-finite directions, or with a learned frame so short before its normalisation that the same step
+// shows in its direction, is decoded in FP32 on the vector ALU by the wave that finds it.
 //
 // Work decomposition and operand layouts are those of the FP16 decode (decode_mfma.h): a wave
 // fetches and decodes chunks of 64 queries on its own, weights in LDS as the A operand, one query
@@ -34,11 +35,12 @@ struct SplitArgs {
     const float* tex;          // FP32 texels (below 4 GiB)
     const uint4* w;            // A blocks in the order of mfma_pack.h, 64 x 16 bytes per part (layer 0: 3 parts)
     const floatx4* bias;       // per (layer, row tile): 4 lane groups x 4 biases, in accumulator scale
-    const half4* wf;           // frame layer: A operand of v_mfma_f32_16x16x16_f16, 64 high, then 64 low
+    const half4* wf;           // frame layer: A operand of v_mfma_f32_16x16x16_f16, 64 x 3 parts
     const floatx4* fbias;      // its biases per lane group, in accumulator scale
     float one;                 // 1.0f (split_pair)
-    float s0;                  // network input scale
-    float finv;                // frame layer accumulator to its value
+    float sz, sd;              // scales of the latent code and of the directions in the network input
+    float finv[4];             // frame layer accumulator to its vectors
+    float shortest2;           // square of the shortest frame vector that stays on the split path
     float c[kMaxLayers];       // half of: accumulator of layer k to the input of layer k + 1
     float oinv[6];             // output accumulator row to q
     int n;
@@ -270,11 +272,12 @@ __global__ void __launch_bounds__((SplitSizes<H, NH, AL>::kW * 64), 1) decode_sp
     uint8_t* const xr = xb + (g >> 1) * 4096 + (g & 1) * 256 + q16 * 16;   // this lane's B operand of tile 0, high halves
     const int t_own = lane >> 4;
 
-    half4 fah = {}, fal = {};
+    half4 fah = {}, fal = {}, far = {};
     floatx4 fb = {0.0f, 0.0f, 0.0f, 0.0f};
     if constexpr (FR) {
         fah = a.wf[lane];
         fal = a.wf[64 + lane];
+        far = a.wf[128 + lane];
         fb = a.fbias[g];
     }
     float2 uv = *chunk_elem<1>(a.uv, n, c * kChunk, lane);
@@ -296,7 +299,7 @@ __global__ void __launch_bounds__((SplitSizes<H, NH, AL>::kW * 64), 1) decode_sp
             for (int k = 0; k < NT; k += 4) {
                 *reinterpret_cast<uint4*>(tb + ((k / 4) * 64 + lane) * 16) = make_uint4(off[k], off[k + 1], off[k + 2], off[k + 3]);
                 *reinterpret_cast<floatx4*>(tb + ((NT / 4 + k / 4) * 64 + lane) * 16) =
-                    floatx4{w[k] * a.s0, w[k + 1] * a.s0, w[k + 2] * a.s0, w[k + 3] * a.s0};
+                    floatx4{w[k] * a.sz, w[k + 1] * a.sz, w[k + 2] * a.sz, w[k + 3] * a.sz};
             }
         }
         float dir[6];
@@ -390,7 +393,9 @@ __global__ void __launch_bounds__((SplitSizes<H, NH, AL>::kW * 64), 1) decode_sp
                         zh = *reinterpret_cast<const half4*>(src);
                         zl = *reinterpret_cast<const half4*>(src + 2048);
                     }
-                    floatx4 o = __builtin_amdgcn_mfma_f32_16x16x16f16(fal, zh, fb, 0, 0, 0);
+                    floatx4 o = __builtin_amdgcn_mfma_f32_16x16x16f16(far, zh, fb, 0, 0, 0);
+                    o = __builtin_amdgcn_mfma_f32_16x16x16f16(fal, zl, o, 0, 0, 0);
+                    o = __builtin_amdgcn_mfma_f32_16x16x16f16(fal, zh, o, 0, 0, 0);
                     o = __builtin_amdgcn_mfma_f32_16x16x16f16(fah, zl, o, 0, 0, 0);
                     o = __builtin_amdgcn_mfma_f32_16x16x16f16(fah, zh, o, 0, 0, 0);
                     if (g < 3) *reinterpret_cast<floatx4*>(tb + ((t * 3 + g) * 16 + q16) * 16) = o;
@@ -401,7 +406,13 @@ __global__ void __launch_bounds__((SplitSizes<H, NH, AL>::kW * 64), 1) decode_sp
                 for (int gg = 0; gg < 3; ++gg) {
                     const floatx4 o = *reinterpret_cast<const floatx4*>(tb + ((t_own * 3 + gg) * 16 + q16) * 16);
                     #pragma unroll
-                    for (int e = 0; e < 4; ++e) v[4 * gg + e] = o[e] * a.finv;
+                    for (int e = 0; e < 4; ++e) v[4 * gg + e] = o[e] * a.finv[(4 * gg + e) / 3];
+                }
+                #pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    if (k >= 2 && a.nf < 2) continue;
+                    const float ss = fmaf(v[3 * k], v[3 * k], fmaf(v[3 * k + 1], v[3 * k + 1], v[3 * k + 2] * v[3 * k + 2]));
+                    bad = bad || (okc && fmaxf(ss, 1e-12f) < a.shortest2);
                 }
                 lds_wave_sync();                                      // tb takes the directions
                 if (a.nf == 2) {
@@ -421,7 +432,7 @@ __global__ void __launch_bounds__((SplitSizes<H, NH, AL>::kW * 64), 1) decode_sp
                 for (int e = 0; e < 8; e += 2) {
                     const int k = 8 * (gg - C / 8) + e;
                     half2_t hh, ll;
-                    split_pair(x[k] * a.s0, x[k + 1] * a.s0, a.one, hh, ll);
+                    split_pair(x[k] * a.sd, x[k + 1] * a.sd, a.one, hh, ll);
                     h[e] = hh[0]; h[e + 1] = hh[1];
                     l[e] = ll[0]; l[e + 1] = ll[1];
                 }

@@ -87,42 +87,41 @@ hipError_t prepare_decode_split(nam_material* m) {
     const MfmaLayout lay = mfma_layout(C, sh.H, NH, true, false);
     const int nB = lay.b_blocks();
     const size_t a_bytes = split_block_offset(lay, sh.H, lay.a_blocks());
-    std::vector<uint8_t> host(a_bytes + (size_t)nB * 64 + (rows_f ? 1024 + 64 : 0), 0);
+    std::vector<uint8_t> host(a_bytes + (size_t)nB * 64 + (rows_f ? 3 * 512 + 64 : 0), 0);
     float* bias = reinterpret_cast<float*>(host.data() + a_bytes);
-    double bound = std::max((double)zmax, dirs);
-    double S = scale_to(32768.0, bound), err = 0.0;
-    if (!usable_scale(S)) return hipSuccess;
+    // Codes and directions have scales of their own: codes far below the directions keep their bits (learned
+    // frames normalise what they give).
+    const double sz = std::min(scale_to(32768.0, (double)zmax), std::ldexp(1.0, 40)), sd = scale_to(32768.0, dirs);
+    if (!usable_scale(sz)) return hipSuccess;
+    double bound = 0.0, S = 1.0, err = 0.0;
     SplitScales sc{};
-    sc.s0 = (float)S;
+    sc.sz = (float)sz;
+    sc.sd = (float)sd;
     size_t off = 0;
     for (int L = 0; L <= NH; ++L) {
         const int fi = m->dims[L], fo = m->dims[L + 1];
         const float* W = m->host_params.data() + off;
         const float* b = W + (size_t)fi * fo;
         off += (size_t)fi * fo + fo;
-        double wmax = 0.0, next = 0.0, norm = 0.0;
+        const auto scale_in = [&](int j) { return L > 0 ? S : j < C ? sz : sd; };
+        double wmax = 0.0, next = 0.0, step = 0.0, top_row[64] = {};
         for (int r = 0; r < fo; ++r) {
             double sum = std::fabs((double)b[r]), sq = 0.0;
             for (int j = 0; j < fi; ++j) {
-                const double w = std::fabs((double)W[(size_t)r * fi + j]);
-                wmax = std::max(wmax, w);
+                const double w = std::fabs((double)W[(size_t)r * fi + j]), e = err + std::ldexp(1.0, -25) / scale_in(j);
+                top_row[r] = std::max(top_row[r], w / scale_in(j));
                 sum += w * (L > 0 ? bound : j < C ? (double)zmax : dirs);
-                sq += w * w;
+                sq += w * w * e * e;
             }
+            wmax = std::max(wmax, top_row[r]);
             next = std::max(next, sum);
-            norm = std::max(norm, std::sqrt(sq));
+            step = std::max(step, std::sqrt(sq));
         }
-        err = (err + std::ldexp(1.0, -25) / S) * norm;
+        err = step;
         // every row of the output layer has a scale of its own (RGB does not depend on an albedo head)
         double T[64];
         for (int r = 0; r < fo; ++r) {
-            double top = wmax;
-            if (L == NH) {
-                top = 0.0;
-                for (int j = 0; j < fi; ++j) top = std::max(top, std::fabs((double)W[(size_t)r * fi + j]));
-            }
-            const double up = scale_to(1023.0, top);
-            T[r] = up * S;
+            T[r] = scale_to(1023.0, L == NH ? top_row[r] : wmax);
             if (!usable_scale(T[r])) return hipSuccess;
         }
         const int rts = L < NH ? lay.RT : 1, kss = L == 0 ? 1 : lay.KS;
@@ -137,12 +136,12 @@ hipError_t prepare_decode_split(nam_material* m) {
                             // slots past 16 inputs: the inputs' last bits, weighed by the high halves
                             in = MfmaLayout::k_source(L, s, lane / 16, x - 4);
                             if (row < fo && in < fi)
-                                put_parts(blk + lane * 16 + 2 * x, 1024, 1, (double)W[(size_t)row * fi + in] * (T[row] / S));
+                                put_parts(blk + lane * 16 + 2 * x, 1024, 1, (double)W[(size_t)row * fi + in] * (T[row] / scale_in(in)));
                             continue;
                         }
                         if (row < fo && in < fi)
                             put_parts(blk + lane * 16 + 2 * x, 1024, L == 0 ? 3 : split_parts(sh.H),
-                                      (double)W[(size_t)row * fi + in] * (T[row] / S));
+                                      (double)W[(size_t)row * fi + in] * (T[row] / scale_in(in)));
                     }
                 }
             }
@@ -163,20 +162,33 @@ hipError_t prepare_decode_split(nam_material* m) {
     // a quarter of the rounding of an FP32 output near 1
     if (!(err <= std::ldexp(1.0, -26))) return hipSuccess;
     if (rows_f) {
+        // a scale per vector (three rows), which its normalisation takes out again
         const float* W = m->host_frames.data();
-        double top = 0.0;
-        for (int i = 0; i < rows_f * C; ++i) top = std::max(top, std::fabs((double)W[i]));
-        const double up = scale_to(1023.0, top), T = up * sc.s0;
-        if (!usable_scale(T)) return hipSuccess;
         uint8_t* wf = host.data() + a_bytes + (size_t)nB * 64;
-        float* fb = reinterpret_cast<float*>(wf + 1024);
+        float* fb = reinterpret_cast<float*>(wf + 3 * 512);
+        double up[4], norm = 0.0;
+        for (int v = 0; v < rows_f / 3; ++v) {
+            double top = 0.0;
+            for (int i = 3 * v * C; i < 3 * (v + 1) * C; ++i) top = std::max(top, std::fabs((double)W[i]));
+            up[v] = scale_to(1023.0, top);
+            if (!usable_scale(up[v]) || !usable_scale(up[v] * sz)) return hipSuccess;
+            sc.finv[v] = (float)(1.0 / (up[v] * sz));
+        }
+        for (int r = 0; r < rows_f; ++r) {
+            double sq = 0.0;
+            for (int c = 0; c < C; ++c) sq += (double)W[r * C + c] * W[r * C + c];
+            norm = std::max(norm, std::sqrt(sq));
+            fb[r] = (float)((double)W[rows_f * C + r] * (up[r / 3] * sz));
+        }
         for (int lane = 0; lane < 64; ++lane)
             for (int x = 0; x < 4; ++x) {
                 const int r = lane % 16, ch = 4 * (lane / 16) + x;
-                if (r < rows_f && ch < C) put_parts(wf + lane * 8 + 2 * x, 512, 2, (double)W[r * C + ch] * up);
+                if (r < rows_f && ch < C) put_parts(wf + lane * 8 + 2 * x, 512, 3, (double)W[r * C + ch] * up[r / 3]);
             }
-        for (int r = 0; r < rows_f; ++r) fb[r] = (float)((double)W[rows_f * C + r] * T);
-        sc.finv = (float)(1.0 / T);
+        // The subnormal step of a code's low halves, 2^-25 / sz per channel, moves a vector by about
+        // 2^-25 norm / sz, as much again for the weights': at this length by an FP32 rounding.
+        const double shortest = 2.0 * norm / sz;
+        sc.shortest2 = (float)std::min(shortest * shortest, 1e38);
     }
     void* dev = nullptr;
     if ((e = hipMalloc(&dev, host.size())) != hipSuccess) return e;
@@ -204,11 +216,13 @@ hipError_t launch_decode_split(const nam_material* m, int64_t n, const float* uv
     a.bias = reinterpret_cast<const floatx4*>(base);
     base += (size_t)lay.b_blocks() * 64;
     a.wf = reinterpret_cast<const half4*>(base);
-    a.fbias = reinterpret_cast<const floatx4*>(base + 1024);
+    a.fbias = reinterpret_cast<const floatx4*>(base + 3 * 512);
     const SplitScales& sc = m->split_scales;
     a.one = 1.0f;
-    a.s0 = sc.s0;
-    a.finv = sc.finv;
+    a.sz = sc.sz;
+    a.sd = sc.sd;
+    std::copy(sc.finv, sc.finv + 4, a.finv);
+    a.shortest2 = sc.shortest2;
     for (int k = 0; k < kMaxLayers; ++k) a.c[k] = 0.5f * sc.c[k];
     std::copy(sc.oinv, sc.oinv + 6, a.oinv);
     a.n = (int)n;

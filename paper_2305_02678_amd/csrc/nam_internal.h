@@ -40,10 +40,12 @@ struct MlpShape {
     int in_dim() const { return C + 6 * dir_groups(); }
 };
 
-// Powers of two of the split FP32 decode (decode_split.h): network input, accumulator of layer k
-// to the input of layer k + 1, output accumulator rows to q, frame layer accumulator to its value.
+// Powers of two of the split FP32 decode (decode_split.h): latent codes and directions to the network
+// input, accumulator of layer k to the input of layer k + 1, output accumulator rows to q, the frame
+// layer's accumulator to its vectors (normal and tangent of each frame); and the square of the shortest
+// such vector that the halves hold to FP32 accuracy.
 struct SplitScales {
-    float s0, c[kMaxLayers], oinv[6], finv;
+    float sz, sd, c[kMaxLayers], oinv[6], finv[4], shortest2;
 };
 
 // Looks up the current device's copy of the static region used by nam_loss_backward_noalloc

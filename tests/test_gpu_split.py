@@ -133,3 +133,24 @@ def test_output_biases_of_any_size(nam, ctx, torch, C, H, NH, nf, albedo, size):
     rows = slice(got.shape[1] - 3, None)
     rel = 1e-5 * np.maximum(1.0, _partial_sums(m, q)[rows])
     assert (np.abs(got - ref)[:, rows] <= np.where(ref[:, rows] > 1.0, 1e-6, rel) * ref[:, rows] + 2.0 ** -150).all()
+
+
+@pytest.mark.parametrize("C,H,NH,nf", [(16, 64, 3, 2), (8, 32, 2, 1), (16, 16, 2, 2)])
+@pytest.mark.parametrize("scale", [1e-3, 1e-5, 1e-7, 1e-9])
+@pytest.mark.parametrize("everywhere", [True, False])
+def test_short_frame_vectors(nam, ctx, torch, C, H, NH, nf, scale, everywhere):
+    """Frames without biases of latents that are small, in the whole texture or in the half of it that
+    the queries see: their normalisation shows every bit that the latents or weights lost.  The frame
+    weights of the normals are a thousand times those of the tangents."""
+    r = wl.rngs(75)
+    m = wl.make_material(r[0], r[1], 32, 32, C, 1, [H] * NH, n_frames=nf)
+    W = r[1].standard_normal((2 * nf, 3, C)) * np.where(np.arange(2 * nf) % 2 == 0, 10.0, 0.01)[:, None, None]
+    m.frame_params = np.concatenate([W.ravel(), np.zeros(6 * nf)]).astype(np.float32)
+    level = np.ascontiguousarray(m.levels[0]).copy()
+    level[:, 0 if everywhere else 16:] *= np.float32(scale)
+    m.levels = [level]
+    q = wl.uniform_queries(r[2], 1000, 0.0, 0.0)
+    q.uv[:, 0] = 0.55 + 0.4 * (q.uv[:, 0] % 1.0)
+    ref = _reference(m, q, None)
+    err = np.abs(nam.decode(nam.Material.from_workload(ctx, m), *nam.to_device(q)).cpu().numpy() - ref) / ref
+    assert (err <= 1e-5 * np.maximum(1.0, _partial_sums(m, q))).all(), err.max()

@@ -84,30 +84,29 @@ __device__ __forceinline__ float relu_twice(float x) { return x + fabsf(x); }
 
 // softplus(q) = max(q, 0) + log1p(e), e = exp(-|q|), to about one rounding.  e = 2^f 2^i from the
 // argument split at its nearest integer, f in two steps (the second adds the low part of log2 e);
-// log1p(e) = 2 atanh(s), s = e / (2 + e) <= 1/3, by the series in s^2 (the first term left out is
-// below 2^-27 of the sum), with the quotient's remainder, that of the rounded 2 + e included, added
-// to the small terms.  Past |q| = 128, where e is below every FP32 number, x stays -128: the split of a
-// larger argument would leave more in f than exp2 takes.  A NaN stays.  Below 2^-25 the result is e, also
-// where halving it would round (subnormal).
+// log1p(e) = 2 atanh(s / 2), s = e / (1 + e / 2) <= 2/3, by the series in s^2 (the first term left out is
+// below 2^-27 of the sum), with the quotient's remainder, that of the rounded 1 + e / 2 included, added
+// to the small terms.  The smallest e (subnormal) pass through unchanged.  Past |q| = 128, where e is
+// below every FP32 number, x stays -128: the split of a larger argument would leave more in f than exp2
+// takes.  A NaN stays.
 __device__ __forceinline__ float softplus_split(float q) {
     const float x = fabsf(q) > 128.0f ? -128.0f : -fabsf(q);
     const float i = __builtin_rintf(x * 1.44269502162933349609375f);
     float f = fmaf(x, 1.44269502162933349609375f, -i);
     f = fmaf(x, 1.92596299e-8f, f);
     const float e = ldexpf(__builtin_amdgcn_exp2f(f), (int)i);
-    const float u = 2.0f + e, ul = e - (u - 2.0f), r = __builtin_amdgcn_rcpf(u);
+    const float u = fmaf(0.5f, e, 1.0f), ul = fmaf(0.5f, e, -(u - 1.0f)), r = __builtin_amdgcn_rcpf(u);
     const float s = e * r;
     const float sl = fmaf(-s, ul, fmaf(-s, u, e)) * r;
     const float t = s * s;
-    float p = 2.0f / 15.0f;
-    p = fmaf(p, t, 2.0f / 13.0f);
-    p = fmaf(p, t, 2.0f / 11.0f);
-    p = fmaf(p, t, 2.0f / 9.0f);
-    p = fmaf(p, t, 2.0f / 7.0f);
-    p = fmaf(p, t, 2.0f / 5.0f);
-    p = fmaf(p, t, 2.0f / 3.0f);
-    const float l = fmaf(2.0f, s, fmaf(s * t, p, 2.0f * sl));
-    return fmaxf(q, 0.0f) + (e < 0x1p-25f ? e : l);
+    float p = 1.0f / (15 << 14);
+    p = fmaf(p, t, 1.0f / (13 << 12));
+    p = fmaf(p, t, 1.0f / (11 << 10));
+    p = fmaf(p, t, 1.0f / (9 << 8));
+    p = fmaf(p, t, 1.0f / (7 << 6));
+    p = fmaf(p, t, 1.0f / (5 << 4));
+    p = fmaf(p, t, 1.0f / (3 << 2));
+    return fmaxf(q, 0.0f) + (s + fmaf(s * t, p, sl));
 }
 
 // Parts of a weight: high and low half, and where a third is kept what those two leave (a weight's

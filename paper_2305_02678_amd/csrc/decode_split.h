@@ -377,8 +377,10 @@ __global__ void __launch_bounds__((SplitSizes<H, NH, AL>::kW * 64), 1) decode_sp
                 fin = fin && dir[d] == dir[d];
             }
             bad = okc && !(fin && m <= kSplitMaxDir);
+            // the output layer sums the tiles' products with zero rows for the other tiles: no lane may bring an
+            // infinity there, also none without a result (past the batch, non-finite uv or lod)
             #pragma unroll
-            for (int d = 0; d < 6; ++d) dir[d] = bad ? 0.0f : dir[d];
+            for (int d = 0; d < 6; ++d) dir[d] = bad || !okc ? 0.0f : dir[d];
             float x[24];
             #pragma unroll
             for (int k = 0; k < 24; ++k) x[k] = 0.0f;

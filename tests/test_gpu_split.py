@@ -154,3 +154,22 @@ def test_short_frame_vectors(nam, ctx, torch, C, H, NH, nf, scale, everywhere):
     ref = _reference(m, q, None)
     err = np.abs(nam.decode(nam.Material.from_workload(ctx, m), *nam.to_device(q)).cpu().numpy() - ref) / ref
     assert (err <= 1e-5 * np.maximum(1.0, _partial_sums(m, q))).all(), err.max()
+
+
+@pytest.mark.parametrize("C,H,NH,nf,albedo,address", SHAPES)
+@pytest.mark.parametrize("size", [100.0, float("inf"), float("nan")])
+def test_large_directions_of_lanes_without_a_result(nam, ctx, torch, C, H, NH, nf, albedo, address, size):
+    """The last query of a ragged batch, which the lanes past its end repeat, and one with a non-finite uv,
+    with directions that no half holds: the other queries are bitwise what they are without them."""
+    r = wl.rngs(78)
+    m = wl.make_material(r[0], r[1], 64, 32, C, 6, [H] * NH, address=address, n_frames=nf, albedo=albedo)
+    q = wl.uniform_queries(r[2], 64 + 9, -0.5, 5.5)
+    q.uv[20, 1] = np.nan
+    mat = nam.Material.from_workload(ctx, m)
+    alone = nam.decode(mat, *nam.to_device(q))
+    q.wi[20], q.wo[72] = size, size
+    got = nam.decode(mat, *nam.to_device(q))
+    keep = torch.ones(73, dtype=torch.bool, device="cuda")
+    keep[[20, 72]] = False
+    assert torch.equal(got[keep], alone[keep]) and torch.isfinite(alone[keep]).all()
+    assert torch.isnan(got[20]).all() and torch.isnan(alone[20]).all()

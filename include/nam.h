@@ -147,8 +147,9 @@ nam_status nam_material_load_file(nam_ctx* ctx, const char* path, nam_material**
  *                         factor split into FP16 halves under exact power-of-two scales, FP32
  *                         accumulation (packed once at load, in device memory the material
  *                         holds).  Materials whose values have no such scales, pyramids of 4 GiB
- *                         and queries with directions beyond unit length (components above 2)
- *                         or non-finite ones run in plain FP32.
+ *                         and queries with direction components above 2^15 or non-finite ones
+ *                         run in plain FP32; queries with components above 2 (directions that
+ *                         are not normalised) are decoded twice.
  *   weights NAM_F16:      FP16 texels, FP16 weights and activations on MFMA, FP32 accumulate.
  *   weights NAM_FP8_E4M3: FP16 texels, OCP E4M3 weights and activations on MFMA with one
  *                         scale per layer for the weights and one for the layer's input, FP32

@@ -12,9 +12,13 @@
 // absolute row sums of the weights: with S_k x_k below 2^15 for every query whose direction
 // components are at most kSplitMaxDir no half can overflow, and the subnormal step of the low
 // half, propagated to the output, stays below the FP32 rounding there.  A material that has no
-// such scales (non-finite or extreme values) keeps the FP32 kernels; a query with larger or
-// non-finite directions, or with a learned frame so short before its normalisation that the same step
-// shows in its direction, is decoded in FP32 on the vector ALU by the wave that finds it.
+// such scales (non-finite or extreme values) keeps the FP32 kernels.
+//
+// A query with larger directions (not normalised) is decoded again with its input and all biases times
+// the power of two that brings them into range, which the ReLUs pass on to the output: exact, and with
+// components up to 2^15 the codes' low halves still reach 2^-25 of the largest code.  A query with
+// directions beyond or not finite, or with a learned frame so short before its normalisation that the
+// halves' step shows in its direction, is decoded in FP32 on the vector ALU by the wave that finds it.
 //
 // Work decomposition and operand layouts are those of the FP16 decode (decode_mfma.h): a wave
 // fetches and decodes chunks of 64 queries on its own, weights in LDS as the A operand, one query
@@ -26,9 +30,12 @@
 #include "decode_mfma.h"
 #include "decode_vec.h"
 
+#include <type_traits>
+
 namespace nam {
 
-constexpr float kSplitMaxDir = 2.0f;      // direction components up to here stay on the split path
+constexpr float kSplitMaxDir = 2.0f;      // direction components up to here stay on the split path as they are,
+constexpr float kSplitFarDir = 32768.0f;  // up to here by a power of two
 
 struct SplitArgs {
     PyrArgs pyr;
@@ -116,21 +123,21 @@ __device__ __forceinline__ float softplus_split(float q) {
 // products): 16 inputs 5.5e-8 / 8.6e-8 / 5.7e-8, 24 6.6 / 8.7 / 6.0, 32 7.5 / 8.9 / 6.2, 64 10.3 / 9.6 / 7.2.
 __host__ __device__ constexpr int split_parts(int inputs) { return inputs <= 32 ? 3 : 2; }
 
-// The chunk's 4 tiles through one row tile: acc[t] = b + W x[t] over KS K steps (the tiles are
+// The chunk's 4 tiles through one row tile: acc[t] = b[t] + W x[t] over KS K steps (the tiles are
 // independent chains).  Small products first, before the roundings of the large ones.
 template <int KS, int P>
 __device__ __forceinline__ void split_tiles(const half8 (&a)[KS][P], const half8 (&bh)[4][KS], const half8 (&bl)[4][KS],
-                                            floatx4 b, floatx4* acc, int stride) {
+                                            const floatx4 (&b)[4], floatx4* acc, int stride) {
     #pragma unroll
     for (int s = 0; s < KS; ++s) {
         if constexpr (P == 3) {
             #pragma unroll
-            for (int t = 0; t < 4; ++t) acc[t * stride] = mfma_f16(a[s][2], bh[t][s], s == 0 ? b : acc[t * stride]);
+            for (int t = 0; t < 4; ++t) acc[t * stride] = mfma_f16(a[s][2], bh[t][s], s == 0 ? b[t] : acc[t * stride]);
             #pragma unroll
             for (int t = 0; t < 4; ++t) acc[t * stride] = mfma_f16(a[s][1], bl[t][s], acc[t * stride]);
         }
         #pragma unroll
-        for (int t = 0; t < 4; ++t) acc[t * stride] = mfma_f16(a[s][1], bh[t][s], P < 3 && s == 0 ? b : acc[t * stride]);
+        for (int t = 0; t < 4; ++t) acc[t * stride] = mfma_f16(a[s][1], bh[t][s], P < 3 && s == 0 ? b[t] : acc[t * stride]);
         #pragma unroll
         for (int t = 0; t < 4; ++t) acc[t * stride] = mfma_f16(a[s][0], bl[t][s], acc[t * stride]);
     }
@@ -271,14 +278,117 @@ __global__ void __launch_bounds__((SplitSizes<H, NH, AL>::kW * 64), 1) decode_sp
     uint8_t* const xr = xb + (g >> 1) * 4096 + (g & 1) * 256 + q16 * 16;   // this lane's B operand of tile 0, high halves
     const int t_own = lane >> 4;
 
-    half4 fah = {}, fal = {}, far = {};
+    half4 fah = {}, fal = {}, fa_rest = {};
     floatx4 fb = {0.0f, 0.0f, 0.0f, 0.0f};
     if constexpr (FR) {
         fah = a.wf[lane];
         fal = a.wf[64 + lane];
-        far = a.wf[128 + lane];
+        fa_rest = a.wf[128 + lane];
         fb = a.fbias[g];
     }
+    // The decoder on the chunk's input in LDS, to the output accumulators of tiles 0-1 and 2-3 (rows as in
+    // decode_mfma_kernel).  scaled: tile t's input comes times f[t], its biases are to follow; fo, fo2: those
+    // of the lane's queries in out and out2.
+    const auto decode = [&](auto scaled, const float (&f)[4], float fo, float fo2, floatx4& out, floatx4& out2) {
+        struct Bias {
+            floatx4 b[4];
+        };
+        const auto bias = [&](int row_tile) {
+            const floatx4 b = sm.bias[row_tile][g];
+            Bias r;
+            #pragma unroll
+            for (int t = 0; t < 4; ++t) r.b[t] = scaled ? b * f[t] : b;
+            return r;
+        };
+        floatx4 acc[4][RT];
+        {
+            half8 bh[4][1], bl[4][1];
+            #pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                bh[t][0] = *reinterpret_cast<const half8*>(xr + t * 512);
+                bl[t][0] = *reinterpret_cast<const half8*>(xr + t * 512 + 2048);
+            }
+            #pragma unroll
+            for (int j = 0; j < RT; ++j) {
+                half8 wa[1][3];
+                #pragma unroll
+                for (int part = 0; part < 3; ++part) wa[0][part] = *reinterpret_cast<const half8*>(&sm.A0[j][part][lane * 16]);
+                split_tiles<1, 3>(wa, bh, bl, bias(j).b, &acc[0][j], RT);
+            }
+        }
+        // output accumulators: tiles 0-1 and 2-3, rows as in decode_mfma_kernel
+        const floatx4 bout = AL ? sm.bias[NH * RT][g & 1] : sm.bias[NH * RT][0];
+        out = scaled ? bout * fo : bout;
+        out2 = scaled ? bout * fo2 : bout;
+        #pragma unroll
+        for (int kk = 0; kk < NH; ++kk) {
+            const float cs = a.c[kk];
+            half8 bh[4][KS], bl[4][KS];
+            #pragma unroll
+            for (int t = 0; t < 4; ++t)
+                #pragma unroll
+                for (int s = 0; s < KS; ++s)
+                    #pragma unroll
+                    for (int e = 0; e < 8; e += 2) {
+                        const int j = 2 * s + e / 4;
+                        half2_t h = {}, l = {}, rest = {};
+                        if (H == 16 && e >= 4) continue;
+                        split_pair(relu_twice(acc[t][j][e % 4]) * cs, relu_twice(acc[t][j][e % 4 + 1]) * cs, a.one, h, l,
+                                   H == 16 ? &rest : nullptr);
+                        if (H == 16) {             // 16 inputs: the other 16 K slots take their last bits
+                            bh[t][s][e + 4] = rest[0]; bh[t][s][e + 5] = rest[1];
+                            bl[t][s][e + 4] = bl[t][s][e + 5] = (_Float16)0.0f;
+                        }
+                        bh[t][s][e] = h[0]; bh[t][s][e + 1] = h[1];
+                        bl[t][s][e] = l[0]; bl[t][s][e + 1] = l[1];
+                    }
+            if (kk < NH - 1) {
+                #pragma unroll
+                for (int j = 0; j < RT; ++j) {
+                    half8 wa[KS][P];
+                    #pragma unroll
+                    for (int s = 0; s < KS; ++s)
+                        #pragma unroll
+                        for (int part = 0; part < P; ++part)
+                            wa[s][part] = *reinterpret_cast<const half8*>(&sm.A[kk * RT * KS + j * KS + s][part][lane * 16]);
+                    split_tiles<KS, P>(wa, bh, bl, bias((kk + 1) * RT + j).b, &acc[0][j], RT);
+                }
+            } else {
+                #pragma unroll
+                for (int low = 1; low >= 0; --low)
+                    #pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        #pragma unroll
+                        for (int s = 0; s < KS; ++s) {
+                            const uint8_t(*wt)[1024] = sm.A[NHB + (AL ? (t & 1) : t) * KS + s];
+                            const half8 ah = *reinterpret_cast<const half8*>(&wt[0][lane * 16]);
+                            floatx4& o = t < 2 ? out : out2;
+                            if (low) {
+                                const half8 al = *reinterpret_cast<const half8*>(&wt[1][lane * 16]);
+                                if constexpr (P == 3) {
+                                    o = mfma_f16(*reinterpret_cast<const half8*>(&wt[2][lane * 16]), bh[t][s], o);
+                                    o = mfma_f16(al, bl[t][s], o);
+                                }
+                                o = mfma_f16(al, bh[t][s], o);
+                                o = mfma_f16(ah, bl[t][s], o);
+                            } else {
+                                o = mfma_f16(ah, bh[t][s], o);
+                            }
+                        }
+            }
+        }
+    };
+    // Largest direction component of the lane's query.
+    const auto largest = [](const float* dir, bool& finite) {
+        float m = 0.0f;
+        finite = true;
+        #pragma unroll
+        for (int d = 0; d < 6; ++d) {
+            m = fmaxf(m, fabsf(dir[d]));
+            finite = finite && dir[d] == dir[d];
+        }
+        return m;
+    };
     float2 uv = *chunk_elem<1>(a.uv, n, c * kChunk, lane);
     float lod = *chunk_elem<1>(a.lod, n, c * kChunk, lane);
     float xi = RR ? *chunk_elem<1>(a.xi, n, c * kChunk, lane) : 0.0f;
@@ -367,16 +477,16 @@ __global__ void __launch_bounds__((SplitSizes<H, NH, AL>::kW * 64), 1) decode_sp
         }
         lds_wave_sync();                                              // the table is spent, z is written
         // ---- directions (or their frame transforms) after z, zeros up to slot 32
-        bool bad;
+        bool bad, far;
         {
-            float m = 0.0f;
-            bool fin = true;
-            #pragma unroll
-            for (int d = 0; d < 6; ++d) {
-                m = fmaxf(m, fabsf(dir[d]));
-                fin = fin && dir[d] == dir[d];
+            bool fin;
+            const float m = largest(dir, fin);
+            bad = okc && !(fin && m <= kSplitFarDir);
+            far = okc && !bad && m > kSplitMaxDir;
+            if (__builtin_expect(__ballot(far) != 0, 0)) {
+                #pragma unroll
+                for (int d = 0; d < 6; ++d) dir[d] = far ? ldexpf(dir[d], 1 - __builtin_amdgcn_frexp_expf(m)) : dir[d];
             }
-            bad = okc && !(fin && m <= kSplitMaxDir);
             // the output layer sums the tiles' products with zero rows for the other tiles: no lane may bring an
             // infinity there, also none without a result (past the batch, non-finite uv or lod)
             #pragma unroll
@@ -394,7 +504,7 @@ __global__ void __launch_bounds__((SplitSizes<H, NH, AL>::kW * 64), 1) decode_sp
                         zh = *reinterpret_cast<const half4*>(src);
                         zl = *reinterpret_cast<const half4*>(src + 2048);
                     }
-                    floatx4 o = __builtin_amdgcn_mfma_f32_16x16x16f16(far, zh, fb, 0, 0, 0);
+                    floatx4 o = __builtin_amdgcn_mfma_f32_16x16x16f16(fa_rest, zh, fb, 0, 0, 0);
                     o = __builtin_amdgcn_mfma_f32_16x16x16f16(fal, zl, o, 0, 0, 0);
                     o = __builtin_amdgcn_mfma_f32_16x16x16f16(fal, zh, o, 0, 0, 0);
                     o = __builtin_amdgcn_mfma_f32_16x16x16f16(fah, zl, o, 0, 0, 0);
@@ -445,111 +555,72 @@ __global__ void __launch_bounds__((SplitSizes<H, NH, AL>::kW * 64), 1) decode_sp
         lds_wave_sync();
 
         // ---- the decoder
+        floatx4 out, out2;
+        const float unscaled[4] = {1.0f, 1.0f, 1.0f, 1.0f};
         __builtin_amdgcn_s_setprio(1);
-        floatx4 acc[4][RT];
-        {
-            half8 bh[4][1], bl[4][1];
-            #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                bh[t][0] = *reinterpret_cast<const half8*>(xr + t * 512);
-                bl[t][0] = *reinterpret_cast<const half8*>(xr + t * 512 + 2048);
-            }
-            #pragma unroll
-            for (int j = 0; j < RT; ++j) {
-                half8 wa[1][3];
+        decode(std::false_type{}, unscaled, 1.0f, 1.0f, out, out2);
+        __builtin_amdgcn_s_setprio(0);
+        const uint64_t badm = __ballot(bad), farm = __ballot(far && !bad);
+        // the results of the queries in `of`, times 2^k of the lane's query
+        const uint64_t okm = __ballot(okc);
+        const auto store = [&](auto scaled, uint64_t of, int k) {
+            if constexpr (AL) {
+                const int half_sel = g & 1;
+                float* dst = a.rgb + 6 * (int64_t)first;
                 #pragma unroll
-                for (int part = 0; part < 3; ++part) wa[0][part] = *reinterpret_cast<const half8*>(&sm.A0[j][part][lane * 16]);
-                split_tiles<1, 3>(wa, bh, bl, sm.bias[j][g], &acc[0][j], RT);
-            }
-        }
-        // output accumulators: tiles 0-1 and 2-3, rows as in decode_mfma_kernel
-        const floatx4 bout = AL ? sm.bias[NH * RT][g & 1] : sm.bias[NH * RT][0];
-        floatx4 out = bout, out2 = bout;
-        #pragma unroll
-        for (int kk = 0; kk < NH; ++kk) {
-            const float cs = a.c[kk];
-            half8 bh[4][KS], bl[4][KS];
-            #pragma unroll
-            for (int t = 0; t < 4; ++t)
-                #pragma unroll
-                for (int s = 0; s < KS; ++s)
-                    #pragma unroll
-                    for (int e = 0; e < 8; e += 2) {
-                        const int j = 2 * s + e / 4;
-                        half2_t h = {}, l = {}, rest = {};
-                        if (H == 16 && e >= 4) continue;
-                        split_pair(relu_twice(acc[t][j][e % 4]) * cs, relu_twice(acc[t][j][e % 4 + 1]) * cs, a.one, h, l,
-                                   H == 16 ? &rest : nullptr);
-                        if (H == 16) {             // 16 inputs: the other 16 K slots take their last bits
-                            bh[t][s][e + 4] = rest[0]; bh[t][s][e + 5] = rest[1];
-                            bl[t][s][e + 4] = bl[t][s][e + 5] = (_Float16)0.0f;
-                        }
-                        bh[t][s][e] = h[0]; bh[t][s][e + 1] = h[1];
-                        bl[t][s][e] = l[0]; bl[t][s][e + 1] = l[1];
-                    }
-            if (kk < NH - 1) {
-                #pragma unroll
-                for (int j = 0; j < RT; ++j) {
-                    half8 wa[KS][P];
-                    #pragma unroll
-                    for (int s = 0; s < KS; ++s)
+                for (int h = 0; h < 2; ++h) {
+                    const floatx4 o = h == 0 ? out : out2;
+                    const int qi = (2 * h + (g >> 1)) * 16 + q16;
+                    const bool okq = (okm >> qi) & 1;
+                    const int kq = scaled ? __shfl(k, qi, 64) : 0;
+                    if (first + qi < n && ((of >> qi) & 1)) {
                         #pragma unroll
-                        for (int part = 0; part < P; ++part)
-                            wa[s][part] = *reinterpret_cast<const half8*>(&sm.A[kk * RT * KS + j * KS + s][part][lane * 16]);
-                    split_tiles<KS, P>(wa, bh, bl, sm.bias[(kk + 1) * RT + j][g], &acc[0][j], RT);
+                        for (int i = 0; i < 4; ++i)
+                            if (i < 2 || !half_sel) {
+                                const float q = o[i] * (half_sel ? a.oinv[i < 2 ? 4 + i : 0] : a.oinv[i]);
+                                dst[6 * qi + 4 * half_sel + i] = okq ? softplus_split(scaled ? ldexpf(q, kq) : q) : __builtin_nanf("");
+                            }
+                    }
                 }
             } else {
+                Rgb v;
+                float* vp = &v.r;
                 #pragma unroll
-                for (int low = 1; low >= 0; --low)
-                    #pragma unroll
-                    for (int t = 0; t < 4; ++t)
-                        #pragma unroll
-                        for (int s = 0; s < KS; ++s) {
-                            const uint8_t(*wt)[1024] = sm.A[NHB + (AL ? (t & 1) : t) * KS + s];
-                            const half8 ah = *reinterpret_cast<const half8*>(&wt[0][lane * 16]);
-                            floatx4& o = t < 2 ? out : out2;
-                            if (low) {
-                                const half8 al = *reinterpret_cast<const half8*>(&wt[1][lane * 16]);
-                                if constexpr (P == 3) {
-                                    o = mfma_f16(*reinterpret_cast<const half8*>(&wt[2][lane * 16]), bh[t][s], o);
-                                    o = mfma_f16(al, bl[t][s], o);
-                                }
-                                o = mfma_f16(al, bh[t][s], o);
-                                o = mfma_f16(ah, bl[t][s], o);
-                            } else {
-                                o = mfma_f16(ah, bh[t][s], o);
-                            }
-                        }
-            }
-        }
-        __builtin_amdgcn_s_setprio(0);
-        const uint64_t badm = __ballot(bad);
-        if constexpr (AL) {
-            const uint64_t okm = __ballot(okc);
-            const int half_sel = g & 1;
-            float* dst = a.rgb + 6 * (int64_t)first;
-            #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const floatx4 o = h == 0 ? out : out2;
-                const int qi = (2 * h + (g >> 1)) * 16 + q16;
-                const bool okq = (okm >> qi) & 1;
-                if (first + qi < n && !((badm >> qi) & 1)) {
-                    #pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (i < 2 || !half_sel)
-                            dst[6 * qi + 4 * half_sel + i] =
-                                okq ? softplus_split(o[i] * (half_sel ? a.oinv[i < 2 ? 4 + i : 0] : a.oinv[i])) : __builtin_nanf("");
+                for (int i = 0; i < 3; ++i) {
+                    const float q = (g < 2 ? out[i] : out2[i]) * a.oinv[i];
+                    const float sp = softplus_split(scaled ? ldexpf(q, k) : q);
+                    vp[i] = okc ? sp : __builtin_nanf("");
                 }
+                if (first + lane < n && ((of >> lane) & 1)) reinterpret_cast<Rgb*>(a.rgb + 3 * (int64_t)first)[lane] = v;
             }
-        } else {
-            Rgb v;
-            float* vp = &v.r;
+        };
+        store(std::false_type{}, ~(badm | farm), 0);
+        if (__builtin_expect(farm != 0, 0)) {                         // uniform, rare
+            int k = 0;
+            if (far) {
+                const float* wi = chunk_elem<3>(a.wi, n, first, lane);
+                const float* wo = chunk_elem<3>(a.wo, n, first, lane);
+                float d6[6] = {wi[0], wi[1], wi[2], wo[0], wo[1], wo[2]};
+                bool fin;
+                k = __builtin_amdgcn_frexp_expf(largest(d6, fin)) - 1;
+            }
+            const float f = ldexpf(1.0f, -k);
+            const _Float16 fh = (_Float16)f;
+            lds_wave_sync();                                          // the input has been read
             #pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                const float sp = softplus_split((g < 2 ? out[i] : out2[i]) * a.oinv[i]);
-                vp[i] = okc ? sp : __builtin_nanf("");
-            }
-            if (first + lane < n && !bad) reinterpret_cast<Rgb*>(a.rgb + 3 * (int64_t)first)[lane] = v;
+            for (int gg = 0; gg < C / 8; ++gg)
+                #pragma unroll
+                for (int part = 0; part < 2; ++part) {
+                    half8* z = reinterpret_cast<half8*>(xb + t_own * 512 + gg * 256 + q16 * 16 + part * 2048);
+                    *z = *z * fh;
+                }
+            lds_wave_sync();
+            float ft[4];
+            #pragma unroll
+            for (int t = 0; t < 4; ++t) ft[t] = __shfl(f, t * 16 + q16, 64);
+            const float fo = AL ? ((g >> 1) ? ft[1] : ft[0]) : f, fo2 = AL ? ((g >> 1) ? ft[3] : ft[2]) : f;
+            decode(std::true_type{}, ft, fo, fo2, out, out2);
+            store(std::true_type{}, farm, k);
         }
         if (badm) {                                                   // uniform, rare
             lds_wave_sync();

@@ -173,3 +173,44 @@ def test_large_directions_of_lanes_without_a_result(nam, ctx, torch, C, H, NH, n
     keep[[20, 72]] = False
     assert torch.equal(got[keep], alone[keep]) and torch.isfinite(alone[keep]).all()
     assert torch.isnan(got[20]).all() and torch.isnan(alone[20]).all()
+
+
+@pytest.mark.parametrize("C,H,NH,nf,albedo,address", SHAPES)
+@pytest.mark.parametrize("length", [2.5, 100.0, 3e4, 1e6])
+def test_directions_of_any_length(nam, ctx, torch, C, H, NH, nf, albedo, address, length):
+    """Directions that are not normalised, on both sides of the largest power of two that the split path
+    takes out; every other query a unit one, which is bitwise what it is alone."""
+    r = wl.rngs(76)
+    m = wl.make_material(r[0], r[1], 64, 32, C, 6, [H] * NH, address=address, n_frames=nf, albedo=albedo)
+    q = wl.uniform_queries(r[2], 777, -0.5, 5.5)
+    mat = nam.Material.from_workload(ctx, m)
+    alone = nam.decode(mat, *nam.to_device(q))
+    q.wi[::2] *= np.float32(length)
+    q.wo[::4] *= np.float32(length)
+    ref = _reference(m, q, None)
+    got = nam.decode(mat, *nam.to_device(q))
+    assert torch.equal(got[1::2], alone[1::2])
+    err = np.abs(got.cpu().numpy() - ref)[::2]
+    assert (err <= 1e-5 * ref[::2] * np.maximum(1.0, _partial_sums(m, q)) + 1e-37).all()
+
+
+def test_time_of_directions_that_are_not_normalised(nam, ctx, torch):
+    """A frame of them takes at most three times as long as one of unit directions (the FP32 kernels that
+    decoded both in the same time took 3.7 times as long; on the vector ALU it would be many times that)."""
+    r = wl.rngs(77)
+    mat = nam.Material.from_workload(ctx, wl.make_material(r[0], r[1], 1024, 1024, 16, 11, [64] * 3))
+    d = nam.to_device(wl.uniform_queries(r[2], 1 << 20, 0.0, 3.0))
+    out, times = None, []
+    for f in (1.0, 3.0):
+        q = (d[0], d[1], d[2] * f, d[3] * f)
+        t = []
+        for _ in range(9):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            out = nam.decode(mat, *q, out=out)
+            e[1].record()
+            torch.cuda.synchronize()
+            t.append(e[0].elapsed_time(e[1]))
+        times.append(sorted(t)[4])
+    print(f"unit directions {times[0]:.3f} ms, of length 3 {times[1]:.3f} ms", flush=True)
+    assert times[1] <= 3.0 * times[0]

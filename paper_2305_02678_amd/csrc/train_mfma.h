@@ -133,7 +133,8 @@ struct TrainLayout {
     static constexpr int FWD = FFB + (NF > 0 ? 16 : 0);            // end of the forward kernel's part
     static constexpr int BF = FWD;                                 // frame layer transposed: [q][lane]
     static constexpr int AW = BF + (NF > 0 ? 3 * 64 : 0);          // exponents of the layers' weight scales (kNoExponent)
-    static constexpr int BLOCKS = AW + 8;                          // blocks of halves
+    static constexpr int BA = AW + 8;                              // BIAS times 2^AW, NaN for units without weights
+    static constexpr int BLOCKS = BA + FF - BIAS;                  // blocks of halves
     static constexpr int A1 = BLOCKS;                              // [j][3 parts][256]
     static constexpr int AH = A1 + HT * 3 * 256;                   // [k][j][s][P][256]
     static constexpr int AH_SZ = HT * KS * P * 256;

@@ -69,11 +69,7 @@ __device__ __forceinline__ float packed_float(const float* __restrict__ p, const
         if (i < NO) return p[oo + i * H + 16 * t + nat(4 * (lane >> 4) + r)];
     } else if (e < L::FF) {
         const int x = e - L::BIAS, k = 1 + x / (HT * 16), y = x % (HT * 16);   // y = slot 16t + 4g + r
-        if (k <= NH) {
-            const int fi = k == 1 ? IN : H, o = (y & ~15) + nat(y & 15);
-            const float b = p[param_off<IN, H>(k) + fi * H + o];
-            return b == 0.0f && no_weights(p + param_off<IN, H>(k) + o * fi, fi) ? __builtin_nanf("") : b;
-        }
+        if (k <= NH) return p[param_off<IN, H>(k) + (k == 1 ? IN : H) * H + (y & ~15) + nat(y & 15)];
         if (y < NO) return p[oo + NO * H + y];
     } else if (e < L::FWD) {
         if (e < L::FFB) {
@@ -111,7 +107,7 @@ __device__ __forceinline__ int weight_exponent(const float* __restrict__ w, int 
     }
     for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
     if (!__builtin_isfinite(m)) return kNoExponent;
-    return m > 0.0f ? min(max(10 - __builtin_amdgcn_frexp_expf(m), -100), 100) : 0;
+    return m > 0.0f ? 10 - __builtin_amdgcn_frexp_expf(m) : 0;
 }
 
 // Packs a decoder: workgroups [0, nf) write the FP32 blocks, a wave of the later ones one block of
@@ -154,9 +150,16 @@ __global__ void __launch_bounds__(256) pack_train_kernel(const float* __restrict
     };
     const auto hidden_slot = [&](int s, int e) { return 16 * (2 * s + e / 4) + nat(4 * g + e % 4); };
     constexpr int KB = HT * KS;                               // blocks of a hidden layer
-    if (b < NH + 1) {                                         // exponents
-        const int aw = exponent(b + 1);
-        if (lane == 0) reinterpret_cast<int*>(blob)[L::AW + b + 1] = aw;
+    if (b < NH + 1) {                                         // exponents, and the biases times 2^exponent
+        const int k = b + 1, aw = exponent(k), fi = fan_in(k), o = 16 * (lane >> 4) + nat(i);
+        const float* w = p + param_off<IN, H>(k);
+        if (lane == 0) reinterpret_cast<int*>(blob)[L::AW + k] = aw;
+        float v = 0.0f;
+        if (k > NH) v = lane < NO ? w[NO * H + lane] : 0.0f;
+        else if (lane < H) v = w[fi * H + o];
+        const bool none = k <= NH && lane < H && v == 0.0f && no_weights(w + o * fi, fi);
+        v = none ? __builtin_nanf("") : ldexpf(v, aw == kNoExponent ? 0 : aw);
+        if (lane < (k > NH ? 16 : H)) blob[L::BA + b * H + lane] = v;
         return;
     }
     b -= NH + 1;
@@ -565,8 +568,9 @@ __device__ __forceinline__ float sample_max(float m) {
     return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
-// Exponent e with 2^e times a sample's largest magnitude m in [2^14, 2^15), as far as 2^e is a float.
-__device__ __forceinline__ int half_exponent(float m) { return min(15 - __builtin_amdgcn_frexp_expf(m), 126); }
+// Exponent e with 2^e times a sample's largest magnitude m in [2^14, 2^15), at most `most` (so that a power
+// of two taken of it is a float).
+__device__ __forceinline__ int half_exponent(float m, int most = 126) { return min(15 - __builtin_amdgcn_frexp_expf(m), most); }
 
 __device__ __forceinline__ float pow2(int e) { return ldexpf(1.0f, e); }
 
@@ -913,10 +917,10 @@ __device__ __forceinline__ void train_front(const TrainArgs& a, const float* lds
             #pragma unroll
             for (int k = 1; k <= NH; ++k) {
                 if (!AHEAD && k > 1) layer.start(block(L::AH) + (k - 2) * L::AH_SZ, lane);
-                const int t0 = aw[k] + (k == 1 ? e0 : ea[k > 1 ? k - 2 : 0]);      // accumulator exponent
-                const float bs = pow2(t0);
+                const int ei = k == 1 ? e0 : ea[k > 1 ? k - 2 : 0], t0 = aw[k] + ei;   // accumulator exponent
+                const float bs = pow2(ei);
                 #pragma unroll
-                for (int t = 0; t < HT; ++t) acc[t] = ld4(block(L::BIAS) + ((k - 1) * HT + t) * 16 + 4 * g) * bs;
+                for (int t = 0; t < HT; ++t) acc[t] = ld4(block(L::BA) + ((k - 1) * HT + t) * 16 + 4 * g) * bs;
                 if (k == 1) layer1.multiply(x0, acc);
                 else layer.multiply(act[k > 1 ? k - 2 : 0], acc);
                 // the next layer's first operands, ahead of the conversions that it waits for
@@ -925,7 +929,7 @@ __device__ __forceinline__ void train_front(const TrainArgs& a, const float* lds
                 tm_range<HT>(acc, most, least);
                 const float m = sample_max(most);
                 near = near || least < m * 0x1p-19f;
-                const int ec = half_exponent(m);
+                const int ec = half_exponent(m, 126 - t0);
                 ea[k - 1] = ec + t0;
                 const float c = pow2(ec);
                 #pragma unroll
@@ -939,7 +943,7 @@ __device__ __forceinline__ void train_front(const TrainArgs& a, const float* lds
                     }
             }
             const int t0 = aw[NH + 1] + ea[NH - 1];
-            floatx4 o = ld4(block(L::BIAS) + NH * HT * 16 + 4 * g) * pow2(t0);
+            floatx4 o = ld4(block(L::BA) + NH * HT * 16 + 4 * g) * pow2(ea[NH - 1]);
             // rows 0..7 of the output blocks: 8 x 16 bytes per lane group
             const float* w = block(L::AO) + (g * 8 + (s & 7)) * 4;
             const auto rows = [&](int at) {

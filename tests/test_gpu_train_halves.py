@@ -171,3 +171,31 @@ def test_infinite_weight_of_an_inactive_unit(nam, torch, C, hidden):
     assert abs(float(loss) - float(loss1)) <= 1e-6 * float(loss1)
     assert torch.isfinite(dz).all() and torch.isfinite(dp).all()
     assert (dz - dz1).norm() <= 1e-6 * dz1.norm() and (dp - dp1).norm() <= 1e-6 * dp1.norm()
+
+
+@pytest.mark.parametrize("C,hidden", [(16, [64] * 3), (8, [32] * 2), (16, [16] * 2)])
+@pytest.mark.parametrize("k", [118, 60, -60, -110])
+def test_layers_of_any_scale(nam, torch, C, hidden, k):
+    """The first layer times 2^k and the second layer's weights times 2^-k, which changes no output: every
+    layer's gradients and the codes' against FP64."""
+    n = 333
+    model, _, par, q, z, keep, net, p64 = _case(torch, nam, C, hidden, n, 101)
+    dims, o, layers = [C + 6] + hidden + [3], 0, []
+    for a, b in zip(dims[:-1], dims[1:]):
+        layers.append((o, o + a * b, o + a * b + b))
+        o += a * b + b
+    with torch.no_grad():
+        p64[layers[0][0]:layers[0][2]] *= 2.0 ** k
+        p64[layers[1][0]:layers[1][1]] *= 2.0 ** -k
+    par.copy_(p64.detach().float())
+    target = torch.rand(n, 3, generator=torch.Generator().manual_seed(102))
+    zz = z.double().requires_grad_()
+    e = torch.where(keep[:, None], net(zz)[0] - target.double(), 0.0)
+    dz, dp = torch.autograd.grad((e ** 2).sum() / e.numel(), (zz, p64))
+    z[~keep] = float("nan")
+    dev = [torch.from_numpy(np.ascontiguousarray(v, np.float32)).cuda() for v in (z.numpy(), q.wi, q.wo)]
+    _, gz, gp = model.loss_backward_codes(par, *dev, target.cuda())
+    gz, gp = gz.cpu().double(), gp.cpu().double()
+    assert (gz - dz).norm() <= 3e-5 * dz.norm()
+    for first, _, last in layers:
+        assert (gp[first:last] - dp[first:last]).norm() <= 3e-5 * dp[first:last].norm()

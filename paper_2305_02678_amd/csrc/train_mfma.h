@@ -13,9 +13,9 @@
 //
 // Arithmetic.  FP32 matrix instructions and vector instructions take turns on a SIMD, so products of
 // FP32 factors run on the FP16 matrix cores, each factor split into two FP16 halves as in the split
-// decode (decode_split.h).  Weights have a power of two per layer (AW); the values of a sample have one
-// per layer, from their own largest magnitude, which puts it in [2^14, 2^15): nothing overflows, and
-// samples of any scale keep their 22 bits beside each other.  In a weight gradient, a sum over
+// decode (decode_split.h).  Weights have a power of two per layer (AW), the values of a sample one per
+// layer, each of which puts their largest magnitude in [2^14, 2^15): nothing overflows, samples of any
+// scale keep their 22 bits beside each other, and so do weights down to 2^-17 of a layer's largest.  In a weight gradient, a sum over
 // samples, every sample's inputs are multiplied by the power of two that brings its product to the
 // scale 2^x of the accumulators; x follows the samples, and the back wave rescales its accumulators when
 // it changes.  The factor is applied in FP16 and so not below 2^-12 (kFarStep): an input's low half

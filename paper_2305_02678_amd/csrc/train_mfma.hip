@@ -93,7 +93,7 @@ __host__ __device__ constexpr int split_input(int g, int e) {
     return d < 6 * (NF > 1 ? NF : 1) ? C + d : -1;
 }
 
-// Exponent that puts a layer's largest weight in [2^9, 2^10) (0 for a layer of zeros); one wave.  With an
+// Exponent that puts a layer's largest weight in [2^14, 2^15) (0 for a layer of zeros); one wave.  With an
 // infinite weight there is none: every tile's forward pass runs in FP32.
 constexpr int kNoExponent = 1000;
 __device__ __forceinline__ int weight_exponent(const float* __restrict__ w, int count, int lane) {
@@ -107,7 +107,7 @@ __device__ __forceinline__ int weight_exponent(const float* __restrict__ w, int 
     }
     for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
     if (!__builtin_isfinite(m)) return kNoExponent;
-    return m > 0.0f ? 10 - __builtin_amdgcn_frexp_expf(m) : 0;
+    return m > 0.0f ? 15 - __builtin_amdgcn_frexp_expf(m) : 0;
 }
 
 // Packs a decoder: workgroups [0, nf) write the FP32 blocks, a wave of the later ones one block of

@@ -199,3 +199,33 @@ def test_layers_of_any_scale(nam, torch, C, hidden, k):
     assert (gz - dz).norm() <= 3e-5 * dz.norm()
     for first, _, last in layers:
         assert (gp[first:last] - dp[first:last]).norm() <= 3e-5 * dp[first:last].norm()
+
+
+@pytest.mark.parametrize("C,hidden", [(16, [64] * 3), (8, [32] * 2), (16, [16] * 2)])
+@pytest.mark.parametrize("k", [12, 20])
+def test_small_weights_beside_a_large_one(nam, torch, C, hidden, k):
+    """One weight 2^k times the others of its layer, on a channel that is always zero: the loss and every
+    gradient but that channel's are those of the other weights."""
+    n = 333
+    model, _, par, q, z, _, _, p64 = _case(torch, nam, C, hidden, n, 103)
+    z[:, 0] = 0.0
+    with torch.no_grad():
+        p64[3 * (C + 6)] = 2.0 ** k
+    par.copy_(p64.detach().float())
+    zz, o = z.double().requires_grad_(), 0
+    x = torch.cat([zz, torch.from_numpy(q.wi).double(), torch.from_numpy(q.wo).double()], 1)
+    keep = torch.ones(n, dtype=torch.bool)
+    dims = [C + 6] + hidden + [3]
+    for i, (a, b) in enumerate(zip(dims[:-1], dims[1:])):
+        y = x @ p64[o:o + a * b].view(b, a).T + p64[o + a * b:o + a * b + b]
+        o += a * b + b
+        keep &= (y.abs().min(1).values > 1e-5 * y.abs().max(1).values) if i < len(hidden) else True
+        x = y.relu()
+    target = torch.rand(n, 3, generator=torch.Generator().manual_seed(104))
+    e = torch.where(keep[:, None], torch.nn.functional.softplus(y) - target.double(), 0.0)
+    dz, dp = torch.autograd.grad((e ** 2).sum() / e.numel(), (zz, p64))
+    z[~keep] = float("nan")
+    dev = [torch.from_numpy(np.ascontiguousarray(v, np.float32)).cuda() for v in (z.numpy(), q.wi, q.wo)]
+    _, gz, gp = model.loss_backward_codes(par, *dev, target.cuda())
+    assert (gz.cpu().double() - dz)[:, 1:].norm() <= 3e-5 * dz[:, 1:].norm()
+    assert (gp.cpu().double() - dp).norm() <= 3e-5 * dp.norm()

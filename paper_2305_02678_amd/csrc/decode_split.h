@@ -96,7 +96,9 @@ __device__ __forceinline__ float relu_twice(float x) { return x + fabsf(x); }
 // to the small terms.  The smallest e (subnormal) pass through unchanged.  Past |q| = 128, where e is
 // below every FP32 number, x stays -128: the split of a larger argument would leave more in f than exp2
 // takes.  A NaN stays.
+// (Contracting s into the last sum would count its rounding twice.)
 __device__ __forceinline__ float softplus_split(float q) {
+    #pragma clang fp contract(off)
     const float x = fabsf(q) > 128.0f ? -128.0f : -fabsf(q);
     const float i = __builtin_rintf(x * 1.44269502162933349609375f);
     float f = fmaf(x, 1.44269502162933349609375f, -i);

@@ -214,3 +214,23 @@ def test_time_of_directions_that_are_not_normalised(nam, ctx, torch):
         times.append(sorted(t)[4])
     print(f"unit directions {times[0]:.3f} ms, of length 3 {times[1]:.3f} ms", flush=True)
     assert times[1] <= 3.0 * times[0]
+
+
+def test_softplus_to_its_roundings(nam, ctx, torch):
+    """Output biases alone (no weights behind them): softplus with one rounding of the result and, below
+    zero, one of the exponential.  A rounding is 2^-24 relative at most, 2.5e-8 in the root mean square
+    over a binade; with half of the values below zero sqrt(1.5) times that, and a tenth for the
+    hardware's exponential."""
+    r = wl.rngs(80)
+    m = wl.make_material(r[0], r[1], 16, 16, 16, 3, [32] * 2)
+    d = nam.to_device(wl.uniform_queries(r[2], 1, 0.0, 1.0))
+    q = np.linspace(-12.0, 12.0, 300).astype(np.float32)
+    m.params[-(3 * 32 + 3):] = 0.0
+    err = []
+    for k in range(0, 300, 3):
+        m.params[-3:] = q[k:k + 3]
+        err.append(nam.decode(nam.Material.from_workload(ctx, m), *d).cpu().numpy()[0])
+    q = q.astype(np.float64)
+    ref = np.maximum(q, 0.0) + np.log1p(np.exp(-np.abs(q)))
+    err = (np.concatenate(err) - ref) / ref
+    assert np.abs(err).max() <= 2.0 ** -23 and np.sqrt((err ** 2).mean()) <= 1.1 * np.sqrt(1.5) * 2.53e-8

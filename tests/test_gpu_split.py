@@ -234,3 +234,21 @@ def test_softplus_to_its_roundings(nam, ctx, torch):
     ref = np.maximum(q, 0.0) + np.log1p(np.exp(-np.abs(q)))
     err = (np.concatenate(err) - ref) / ref
     assert np.abs(err).max() <= 2.0 ** -23 and np.sqrt((err ** 2).mean()) <= 1.1 * np.sqrt(1.5) * 2.53e-8
+
+
+@pytest.mark.parametrize("C,H,NH,nf,albedo,address", [(16, 64, 3, 2, False, wl.WRAP), (8, 32, 2, 1, False, wl.CLAMP),
+                                                      (16, 32, 2, 0, True, wl.WRAP), (8, 16, 1, 2, True, wl.WRAP)])
+@pytest.mark.parametrize("stochastic", [False, True])
+def test_frames_and_albedo_without_scales(nam, ctx, torch, C, H, NH, nf, albedo, address, stochastic):
+    """One texel beyond any FP16 scale, which no query reaches: the FP32 kernels that the split path
+    leaves to such materials."""
+    r = wl.rngs(79)
+    m = wl.make_material(r[0], r[1], 64, 64, C, 6, [H] * NH, address=address, n_frames=nf, albedo=albedo)
+    m.levels[0][0, 0, 0] = 1e38
+    q = wl.uniform_queries(r[2], 700, 1.0, 5.5)
+    xi = r[4].random(700).astype(np.float32) if stochastic else None
+    ref = _reference(m, q, xi)
+    got = nam.decode(nam.Material.from_workload(ctx, m), *nam.to_device(q),
+                     xi=None if xi is None else torch.from_numpy(xi).cuda()).cpu().numpy()
+    m.levels[0][0, 0, 0] = 0.0                          # (not in the partial sums)
+    assert (np.abs(got - ref) <= 1e-5 * ref * np.maximum(1.0, _partial_sums(m, q))).all()

@@ -701,7 +701,11 @@ class Server:
 
     def reset_stats(self):
         check(lib().nam_server_reset_stats(self.handle))
-        self._keep.clear()
+        # the buffers of requests that are not finished stay in use
+        done = ctypes.c_int(0)
+        for ticket in list(self._keep):
+            if _lib.nam_server_poll(self.handle, ticket, ctypes.byref(done), None) == NAM_E_INVALID_ARG:
+                del self._keep[ticket]
 
     def close(self):
         if self.handle:

@@ -48,3 +48,29 @@ def test_concurrent_submissions(precision):
     for m, q, rgb in (j for t in jobs for j in t):
         assert torch.equal(rgb, nam.decode(mats[m][0], *q))
     server.close()
+
+
+def test_reset_keeps_the_buffers_of_waiting_requests():
+    """A request that has not finished when the statistics are reset keeps its tensors, whatever the
+    caller does with its own references; a finished one gives them back."""
+    import torch
+    from paper_2305_02678_amd import nam
+    ctx = nam.Context(0)
+    server = nam.Server(ctx, n_streams=2, max_tile=2048)
+    r = wl.rngs(94)
+    m = nam.Material.from_workload(ctx, wl.make_material(r[0], r[1], 64, 64, 16, 4, [32] * 2))
+    mid = server.add_material(m)
+    q = nam.to_device(wl.uniform_queries(r[2], 3000, -0.5, 3.5))
+    first, late = (torch.full((3000, 3), -1.0, device="cuda") for _ in range(2))
+    a = server.submit(mid, *q, first)
+    server.wait_all()
+    b = server.submit(mid, *q, late, arrival_s=0.3)
+    server.reset_stats()
+    assert a not in server._keep and b in server._keep
+    with pytest.raises(nam.NamError):
+        server.poll(a)
+    server.wait_all()
+    assert server.poll(b)[0] and torch.equal(late, nam.decode(m, *q))
+    server.reset_stats()
+    assert not server._keep
+    server.close()

@@ -58,6 +58,7 @@ class AdamCfg(ctypes.Structure):
 
 _lib = None
 _torch = None          # set with _lib: the per-call paths below import and look up nothing
+_current_stream = None
 
 
 def header_functions() -> List[str]:
@@ -69,11 +70,12 @@ def header_functions() -> List[str]:
 def lib(build_if_missing: bool = False):
     """Load libnam.so once.  torch is imported first so that the library binds to the HIP
     runtime torch already loaded (one runtime per process)."""
-    global _lib, _torch
+    global _lib, _torch, _current_stream
     if _lib is not None:
         return _lib
     import torch  # (HIP runtime first)
     _torch = torch
+    _current_stream = _current_stream_of(torch)
     if not os.path.exists(LIB_PATH):
         if not build_if_missing:
             raise RuntimeError(f"libnam is not built ({LIB_PATH} missing); run python -m paper_2305_02678_amd.build")
@@ -146,12 +148,19 @@ def check(status: int):
         raise NamError(status, lib().nam_last_error().decode())
 
 
+def _current_stream_of(torch):
+    """A function returning the current hipStream_t: through torch's raw accessors where this torch
+    has them, else through its stream object (3 us of every call)."""
+    raw = torch._C
+    stream, device = getattr(raw, "_cuda_getCurrentRawStream", None), getattr(raw, "_cuda_getDevice", None)
+    if stream is None or device is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: stream(device())
+
+
 def _stream(stream=None):
     """The hipStream_t of a torch stream, or of the current one."""
-    if stream is not None:
-        return stream.cuda_stream
-    raw = _torch._C
-    return raw._cuda_getCurrentRawStream(raw._cuda_getDevice())
+    return stream.cuda_stream if stream is not None else _current_stream()
 
 
 def _dev(t, shape_tail, name):

@@ -86,3 +86,20 @@ def test_null_arguments_of_the_material_file_sampler_and_frame_calls(L):
     assert L.nam_proxy_pdf(None, 0, None, None, None, None, None) == nam.NAM_E_INVALID_ARG
     assert L.nam_proxy_sample(None, 0, None, None, None, None, None, None) == nam.NAM_E_INVALID_ARG
     assert L.nam_decode_stochastic(None, None, 0, None, None, None, None, None, None, None) == nam.NAM_E_INVALID_ARG
+
+
+def test_current_stream_with_and_without_torchs_raw_accessors():
+    class Object:
+        pass
+
+    def torch_with(**raw):
+        t = Object()
+        t._C = Object()
+        t._C.__dict__.update(raw)
+        t.cuda = Object()
+        t.cuda.current_stream = lambda: type("Stream", (), {"cuda_stream": 77})()
+        return t
+
+    assert nam._current_stream_of(torch_with(_cuda_getCurrentRawStream=lambda d: 100 + d, _cuda_getDevice=lambda: 3))() == 103
+    assert nam._current_stream_of(torch_with(_cuda_getDevice=lambda: 3))() == 77
+    assert nam._current_stream_of(torch_with())() == 77

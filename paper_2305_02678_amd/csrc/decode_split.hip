@@ -34,13 +34,33 @@ static double scale_to(double top, double x) {
 
 static bool usable_scale(double s) { return s >= std::ldexp(1.0, -100) && s <= std::ldexp(1.0, 100); }
 
-// The parts of v (a float times a power of two), `stride` bytes apart.
-static void put_parts(uint8_t* dst, size_t stride, int parts, double v) {
-    float rest = (float)v;
+// FP16 of |x| < 32768, round to nearest even, and back.  (The host's _Float16 conversions are library
+// calls, most of the time of packing a decoder of three layers of 64.)
+static uint16_t half_bits(float x) {
+    uint32_t u;
+    std::memcpy(&u, &x, 4);
+    const uint16_t sign = (uint16_t)((u >> 16) & 0x8000);
+    const uint32_t a = u & 0x7fffffffu;
+    if (a >= 0x38800000u)                       // normal, from 2^-14
+        return sign | (uint16_t)((a + 0xfffu + ((a >> 13) & 1u) - 0x38000000u) >> 13);
+    const float s = std::fabs(x) + 0.5f;        // its last place is 2^-24
+    std::memcpy(&u, &s, 4);
+    return sign | (uint16_t)(u - 0x3f000000u);
+}
+
+static float half_value(uint16_t h) {
+    const uint32_t m = h & 0x7fff, u = (m << 13) + 0x38000000u;
+    float v = (float)m * 0x1p-24f;
+    if (m >= 0x400) std::memcpy(&v, &u, 4);
+    return h & 0x8000 ? -v : v;
+}
+
+// The parts of v (a weight times a power of two), `stride` bytes apart.
+static void put_parts(uint8_t* dst, size_t stride, int parts, float v) {
     for (int i = 0; i < parts; ++i) {
-        const _Float16 h = (_Float16)rest;
+        const uint16_t h = half_bits(v);
         std::memcpy(dst + i * stride, &h, 2);
-        rest -= (float)h;                       // exact
+        v -= half_value(h);                     // exact
     }
 }
 
@@ -50,29 +70,52 @@ static size_t split_block_offset(const MfmaLayout& lay, int H, int block) {
     return b0 * 3072 + (block - b0) * 1024 * split_parts(H);
 }
 
+// Largest |texel| of the material as float bits; `word`: four bytes of device memory.
+static hipError_t texel_absmax(const nam_material* m, unsigned int* word, unsigned int* bits) {
+    hipError_t e = hipMemset(word, 0, sizeof(unsigned int));
+    if (e != hipSuccess) return e;
+    clear_stale_hip_error();
+    const int64_t count = m->texel_count * m->desc.channels / 4;
+    const int blocks = (int)std::min<int64_t>(m->ctx->cu_count * 8, (count + 255) / 256);
+    absmax_kernel<<<blocks, 256, 0, nullptr>>>(reinterpret_cast<const uint4*>(m->texels32), count, word);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    return hipMemcpy(bits, word, sizeof(unsigned int), hipMemcpyDeviceToHost);
+}
+
+// Packs the decoder behind `dev`, which holds `host.size()` bytes; *packed tells whether it has scales.
+static hipError_t pack_decode_split(nam_material* m, void* dev, std::vector<uint8_t>& host, bool* packed);
+
 hipError_t prepare_decode_split(nam_material* m) {
     const MlpShape& sh = m->shape;
-    const int C = sh.C, NH = sh.NH, NO = sh.NO, rows_f = 6 * sh.NF;
     // 32-bit byte offsets into the FP32 texels
-    if (m->texel_count * C * 4 >= (int64_t(1) << 32)) return hipSuccess;
+    if (m->texel_count * sh.C * 4 >= (int64_t(1) << 32)) return hipSuccess;
     for (float p : m->host_params)
         if (!std::isfinite(p)) return hipSuccess;
     for (float p : m->host_frames)
         if (!std::isfinite(p)) return hipSuccess;
-
-    unsigned int* dmax = nullptr;
-    hipError_t e = hipMalloc(&dmax, sizeof(unsigned int));
+    const MfmaLayout lay = mfma_layout(sh.C, sh.H, sh.NH, true, false);
+    std::vector<uint8_t> host(split_block_offset(lay, sh.H, lay.a_blocks()) + (size_t)lay.b_blocks() * 64 + (sh.NF ? 3 * 512 + 64 : 0), 0);
+    // one allocation for the search of the largest texel and for the blocks: a load's allocations are most
+    // of what it costs (a material of 64 x 64 x 8)
+    void* dev = nullptr;
+    hipError_t e = hipMalloc(&dev, host.size());
     if (e != hipSuccess) return e;
-    unsigned int bits = 0;
-    e = hipMemset(dmax, 0, sizeof(unsigned int));
-    if (e == hipSuccess) {
-        clear_stale_hip_error();
-        absmax_kernel<<<m->ctx->cu_count * 8, 256, 0, nullptr>>>(reinterpret_cast<const uint4*>(m->texels32),
-                                                                 m->texel_count * C / 4, dmax);
-        e = hipGetLastError();
+    bool packed = false;
+    e = pack_decode_split(m, dev, host, &packed);
+    if (e != hipSuccess || !packed) {
+        (void)hipFree(dev);
+        return e;
     }
-    if (e == hipSuccess) e = hipMemcpy(&bits, dmax, sizeof(bits), hipMemcpyDeviceToHost);
-    (void)hipFree(dmax);
+    m->split = dev;
+    m->split_bytes = host.size();
+    return hipSuccess;
+}
+
+static hipError_t pack_decode_split(nam_material* m, void* dev, std::vector<uint8_t>& host, bool* packed) {
+    const MlpShape& sh = m->shape;
+    const int C = sh.C, NH = sh.NH, NO = sh.NO, rows_f = 6 * sh.NF;
+    unsigned int bits = 0;
+    hipError_t e = texel_absmax(m, static_cast<unsigned int*>(dev), &bits);
     if (e != hipSuccess) return e;
     float zmax;
     std::memcpy(&zmax, &bits, 4);
@@ -87,7 +130,6 @@ hipError_t prepare_decode_split(nam_material* m) {
     const MfmaLayout lay = mfma_layout(C, sh.H, NH, true, false);
     const int nB = lay.b_blocks();
     const size_t a_bytes = split_block_offset(lay, sh.H, lay.a_blocks());
-    std::vector<uint8_t> host(a_bytes + (size_t)nB * 64 + (rows_f ? 3 * 512 + 64 : 0), 0);
     float* bias = reinterpret_cast<float*>(host.data() + a_bytes);
     // Codes and directions have scales of their own: codes far below the directions keep their bits (learned
     // frames normalise what they give).
@@ -105,13 +147,19 @@ hipError_t prepare_decode_split(nam_material* m) {
         off += (size_t)fi * fo + fo;
         const auto scale_in = [&](int j) { return L > 0 ? S : j < C ? sz : sd; };
         double wmax = 0.0, next = 0.0, step = 0.0, top_row[64] = {};
+        double in_scale[64], in_bound[64], in_err[64];             // per input: 1 / scale, bound, error
+        for (int j = 0; j < fi; ++j) {
+            in_scale[j] = 1.0 / scale_in(j);
+            in_bound[j] = L > 0 ? bound : j < C ? (double)zmax : dirs;
+            in_err[j] = err + 0x1p-25 * in_scale[j];
+        }
         for (int r = 0; r < fo; ++r) {
             double sum = std::fabs((double)b[r]), sq = 0.0;
             for (int j = 0; j < fi; ++j) {
-                const double w = std::fabs((double)W[(size_t)r * fi + j]), e = err + std::ldexp(1.0, -25) / scale_in(j);
-                top_row[r] = std::max(top_row[r], w / scale_in(j));
-                sum += w * (L > 0 ? bound : j < C ? (double)zmax : dirs);
-                sq += w * w * e * e;
+                const double w = std::fabs((double)W[(size_t)r * fi + j]), e = w * in_err[j];
+                top_row[r] = std::max(top_row[r], w * in_scale[j]);
+                sum += w * in_bound[j];
+                sq += e * e;
             }
             wmax = std::max(wmax, top_row[r]);
             next = std::max(next, sum);
@@ -130,18 +178,19 @@ hipError_t prepare_decode_split(nam_material* m) {
                 uint8_t* blk = host.data() + split_block_offset(lay, sh.H, lay.a_index(L, j, s));
                 for (int lane = 0; lane < 64; ++lane) {
                     const int row = 16 * j + lane % 16;
+                    if (row >= fo) continue;
+                    const double up = T[row] / scale_in(0), up_dirs = T[row] / scale_in(C);   // (the same past layer 0)
                     for (int x = 0; x < 8; ++x) {
                         int in = MfmaLayout::k_source(L, s, lane / 16, x);
+                        int parts = L == 0 ? 3 : split_parts(sh.H);
                         if (L > 0 && sh.H == 16 && x >= 4) {
                             // slots past 16 inputs: the inputs' last bits, weighed by the high halves
                             in = MfmaLayout::k_source(L, s, lane / 16, x - 4);
-                            if (row < fo && in < fi)
-                                put_parts(blk + lane * 16 + 2 * x, 1024, 1, (double)W[(size_t)row * fi + in] * (T[row] / scale_in(in)));
-                            continue;
+                            parts = 1;
                         }
-                        if (row < fo && in < fi)
-                            put_parts(blk + lane * 16 + 2 * x, 1024, L == 0 ? 3 : split_parts(sh.H),
-                                      (double)W[(size_t)row * fi + in] * (T[row] / scale_in(in)));
+                        if (in < fi)
+                            put_parts(blk + lane * 16 + 2 * x, 1024, parts,
+                                      (float)((double)W[(size_t)row * fi + in] * (in < C ? up : up_dirs)));
                     }
                 }
             }
@@ -183,22 +232,16 @@ hipError_t prepare_decode_split(nam_material* m) {
         for (int lane = 0; lane < 64; ++lane)
             for (int x = 0; x < 4; ++x) {
                 const int r = lane % 16, ch = 4 * (lane / 16) + x;
-                if (r < rows_f && ch < C) put_parts(wf + lane * 8 + 2 * x, 512, 3, (double)W[r * C + ch] * up[r / 3]);
+                if (r < rows_f && ch < C) put_parts(wf + lane * 8 + 2 * x, 512, 3, (float)((double)W[r * C + ch] * up[r / 3]));
             }
         // The subnormal step of a code's low halves, 2^-25 / sz per channel, moves a vector by about
         // 2^-25 norm / sz, as much again for the weights': at this length by an FP32 rounding.
         const double shortest = 2.0 * norm / sz;
         sc.shortest2 = (float)std::min(shortest * shortest, 1e38);
     }
-    void* dev = nullptr;
-    if ((e = hipMalloc(&dev, host.size())) != hipSuccess) return e;
-    if ((e = hipMemcpy(dev, host.data(), host.size(), hipMemcpyHostToDevice)) != hipSuccess) {
-        (void)hipFree(dev);
-        return e;
-    }
-    m->split = dev;
-    m->split_bytes = host.size();
+    if ((e = hipMemcpy(dev, host.data(), host.size(), hipMemcpyHostToDevice)) != hipSuccess) return e;
     m->split_scales = sc;
+    *packed = true;
     return hipSuccess;
 }
 

@@ -15,8 +15,12 @@
 // FP32 factors run on the FP16 matrix cores, each factor split into two FP16 halves as in the split
 // decode (decode_split.h).  Weights have a power of two per layer (AW), the values of a sample one per
 // layer, each of which puts their largest magnitude in [2^14, 2^15): nothing overflows, samples of any
-// scale keep their 22 bits beside each other, and so do weights down to 2^-17 of a layer's largest.  In a weight gradient, a sum over
-// samples, every sample's inputs are multiplied by the power of two that brings its product to the
+// scale keep their 22 bits beside each other, and so do weights down to 2^-17 of a layer's largest.  Two
+// halves lose the last bit of a quarter of the weights, a tie of the low half's rounding.  The loss would
+// be the same for every sample and add up over them, so the odd workgroups hold the tie's other neighbour:
+// the two errors are opposite (ALT).
+//
+// In a weight gradient, a sum over samples, every sample's inputs are multiplied by the power of two that brings its product to the
 // scale 2^x of the accumulators; x follows the samples, and the back wave rescales its accumulators when
 // it changes.  The factor is applied in FP16 and so not below 2^-12 (kFarStep): an input's low half
 // keeps its bits down to 2^-5 of the sample's largest there, and loses 2^-28 of the largest below.  A
@@ -141,8 +145,10 @@ struct TrainLayout {
     static constexpr int AO = AH + (NH - 1) * AH_SZ;               // [s][P][128]
     static constexpr int BO = AO + KS * P * 128;                   // W_out^T: [j][P][64]
     static constexpr int B1 = BO + HT * P * 64;                    // W_1^T: [u][s][P][256]
-    static constexpr int BLOB = B1 + NR1 * KS * P * 256;
-    static constexpr int LDS_FLOATS = BLOB - BIAS;                 // the training kernel's part
+    static constexpr int END = B1 + NR1 * KS * P * 256;
+    static constexpr int LDS_FLOATS = END - BIAS;                  // the training kernel's part
+    static constexpr int ALT = P == 2 ? END - BLOCKS : 0;          // the odd workgroups' blocks lie this far on
+    static constexpr int BLOB = END + ALT;
     static constexpr int XCH = NF > 0 ? 16 * 12 : 0;   // per front wave: values handed across lanes
     static_assert(BIAS % 4 == 0 && FWD % 4 == 0 && BLOCKS % 4 == 0 && BLOB % 4 == 0, "16-byte alignment of blocks");
 };

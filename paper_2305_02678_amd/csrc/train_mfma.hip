@@ -144,7 +144,13 @@ __global__ void __launch_bounds__(256) pack_train_kernel(const float* __restrict
             for (int part = 0; part < parts; ++part) {
                 const _Float16 h = (_Float16)rest;
                 *reinterpret_cast<_Float16*>(d + part * stride + 2 * e) = h;
-                rest -= (float)h;
+                const float left = rest - (float)h;
+                if (L::ALT) {
+                    const _Float16 other = (_Float16)(rest + left);         // exact where h rounded a tie
+                    const bool tie = part == parts - 1 && (float)other - rest == left;
+                    *reinterpret_cast<_Float16*>(d + L::ALT * 4 + part * stride + 2 * e) = tie ? other : h;
+                }
+                rest = left;
             }
         }
     };
@@ -1450,7 +1456,9 @@ __global__ void __launch_bounds__(kTMThreads, 1) train_mfma_kernel(const TrainAr
     __shared__ TmSmem<C, H, NH, NF> sm;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    for (int e = tid; e < L::LDS_FLOATS / 4; e += kTMThreads) st4(sm.blocks + 4 * e, ld4(a.blob + L::BIAS + 4 * e));
+    const int alt = (blockIdx.x & 1) * L::ALT;
+    for (int e = tid; e < L::LDS_FLOATS / 4; e += kTMThreads)
+        st4(sm.blocks + 4 * e, ld4(a.blob + L::BIAS + 4 * e + (4 * e >= L::BLOCKS - L::BIAS ? alt : 0)));
     if (tid < a.M) sm.rows[tid] = a.rows[tid];
     if (tid < 2 * kTMPairs) sm.counts[tid / kTMPairs][tid % kTMPairs] = 0;
     __syncthreads();

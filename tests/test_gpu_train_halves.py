@@ -229,3 +229,20 @@ def test_small_weights_beside_a_large_one(nam, torch, C, hidden, k):
     _, gz, gp = model.loss_backward_codes(par, *dev, target.cuda())
     assert (gz.cpu().double() - dz)[:, 1:].norm() <= 3e-5 * dz[:, 1:].norm()
     assert (gp.cpu().double() - dp).norm() <= 3e-5 * dp.norm()
+
+
+@pytest.mark.parametrize("C,hidden", [(16, [64] * 3), (8, [64] * 2), (16, [64]), (16, [32] * 3), (8, [16] * 2)])
+def test_sum_of_the_codes_gradients(nam, torch, C, hidden):
+    """Gradients of one sign, summed over 65,536 samples: what a rounding does alike to every sample (of a
+    weight, above all) stays in the sum, the rest averages out.  One rounding, 2^-24, is left for the
+    loss's factor and the softplus."""
+    n = 65536
+    model, _, par, q, z, keep, net, _ = _case(torch, nam, C, hidden, n, 200)
+    target = torch.full((n, 3), -100.0)
+    zz = z.double().requires_grad_()
+    e = torch.where(keep[:, None], net(zz)[0] - target.double(), 0.0)
+    total = torch.autograd.grad((e ** 2).sum() / e.numel(), zz)[0].sum(0)
+    z[~keep] = float("nan")
+    dev = [torch.from_numpy(np.ascontiguousarray(v, np.float32)).cuda() for v in (z.numpy(), q.wi, q.wo)]
+    got = model.loss_backward_codes(par, *dev, target.cuda())[1].cpu().double().sum(0)
+    assert (got - total).norm() <= 2.0 ** -24 * total.norm()

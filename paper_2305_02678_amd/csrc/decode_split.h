@@ -218,12 +218,12 @@ __device__ __forceinline__ void decode_lanes_f32(const SplitArgs& a, float* tabl
     }
 }
 
-// One workgroup of 8 waves per CU, 250 registers (three waves per SIMD spilled at 168 and were no
+// One workgroup of 8 waves per CU, 254 registers (three waves per SIMD spilled at 168 and were no
 // faster).  Measured, 22-64-64-64-3 on the 1080p frame of a 2048^2 x 16 texture: 155 us (592 us on the
-// FP32 matrix cores), error against 64 bits 4.5e-8 (7.8e-8); 20-32-32-3 with two frames and the
-// stochastic filter, 500,009 queries: 22.4 us (57.5 us on the vector ALU), 4.3e-8 (4.6e-8).  Without its
-// texel loads the frame takes 110 us: per 64 queries a SIMD issues 264 matrix-core instructions (4,224
-// cycles of the matrix pipe) and about 1,150 vector ones (4,700 cycles) through one port, and twice the
+// FP32 matrix cores), error against 64 bits 4.3e-8 (7.8e-8); 20-32-32-3 with two frames and the
+// stochastic filter, 500,009 queries: 23.8 us (57.5 us on the vector ALU), 4.2e-8 (4.3e-8).  Without its
+// texel loads the frame took 110 us: per 64 queries a SIMD issues 296 matrix-core instructions (4,736
+// cycles of the matrix pipe) and 1,244 vector ones (about 5,000 cycles) through one port, and twice the
 // FP16 decode's texel bytes come from beyond the L2.
 template <int C, int H, int NH, bool RR, bool FR, bool AL>
 __global__ void __launch_bounds__((SplitSizes<H, NH, AL>::kW * 64), 1) decode_split_kernel(const SplitArgs a) {

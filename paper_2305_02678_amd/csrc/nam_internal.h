@@ -163,10 +163,10 @@ hipError_t launch_decode_f32(const nam_material* m, int64_t n, const float* uv, 
 hipError_t prepare_decode_split(nam_material* m);
 hipError_t launch_decode_split(const nam_material* m, int64_t n, const float* uv, const float* lod, const float* xi,
                                const float* wi, const float* wo, float* rgb, hipStream_t s);
-// Materials without a split decoder: plain trilinear FP32 decodes on the FP32 matrix cores (the training kernel's forward), for the
-// decoders that kernel takes (C in {8, 16}, H in {32, 64}, 2 or 3 hidden layers, 3 or 6
-// outputs, no frames; 32-bit texel offsets): prepare packs the decoder into m->fblob once and
-// leaves it null where unsupported; the launch needs it (n below 2^31).
+// Materials without a split decoder: plain trilinear FP32 decodes on the FP32 matrix cores (the training
+// kernel's forward), for the decoders without frames that kernel takes (hidden widths 16, 32 and 64, but
+// for four layers of 64; 3 or 6 outputs) and 32-bit texel offsets: prepare packs the decoder into m->fblob
+// once and leaves it null where unsupported; the launch needs it (n below 2^31).
 hipError_t prepare_decode_f32_mfma(nam_material* m);
 hipError_t launch_decode_f32_mfma(const nam_material* m, int64_t n, const float* uv, const float* lod, const float* wi,
                                   const float* wo, float* rgb, hipStream_t s);

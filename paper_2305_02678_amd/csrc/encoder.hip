@@ -61,7 +61,7 @@ __device__ __forceinline__ bool enc_input(const EncoderArgs& a, const LevelRow* 
 // ---- forward
 //
 // What bounds it: the random texels, 8 per item at uniform queries: 2^20 items at 4-32-32-16 over a
-// 1024 x 1024 pyramid of 22 MB take 83 us (one item per lane with the layers on the vector ALU and a
+// 1024 x 1024 pyramid of 22 MB take 81 us (one item per lane with the layers on the vector ALU and a
 // code written 64 bytes apart per lane 89 us), the 100,003 of an encoder of width 16 10 us less.
 constexpr int kEncFwdWaves = 4;
 
@@ -155,7 +155,7 @@ __global__ void __launch_bounds__(64 * kEncFwdWaves) encoder_forward_kernel(cons
 //
 // What bounds it: FP32 matrix and vector instructions, which take turns on a SIMD: at 4-32-32-16 86 of
 // the former at 32 cycles per tile, 73 us of 2^20 samples.  One sample per lane with the layers on the
-// vector ALU and one wave per SIMD took 371 us; this takes 144 us, 83 us of it the forward kernel's
+// vector ALU and one wave per SIMD took 371 us; this takes 130 us, 81 us of it the forward kernel's
 // fetch.
 constexpr int kEncWaves = 8;
 constexpr int kES = 17;                        // LDS row stride: the 16 samples of a tile, one bank apart

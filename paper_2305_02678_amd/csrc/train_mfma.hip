@@ -1029,6 +1029,7 @@ __device__ __forceinline__ void train_front(const TrainArgs& a, const float* lds
         const float dq_most = fmaxf(fabsf(dq[0]), fabsf(dq[1]));
         transpose_groups(dq);
         half2_t th[4][2], tl[4][2], uh[4][2], ul[4][2];          // handoff operands by tile
+        half2_t dr[2];                                            // what the output deltas' halves leave
         TmHalves<KS> d;                                           // the layer's deltas as B operands
         int ed, eds;                                              // their exponent; kNoSample where they are zero
         {
@@ -1037,7 +1038,7 @@ __device__ __forceinline__ void train_front(const TrainArgs& a, const float* lds
             eds = m > 0.0f ? ed : kNoSample;
             #pragma unroll
             for (int j = 0; j < 2; ++j)
-                split_pair(ldexpf(sign * dq[2 * j], ed), ldexpf(sign * dq[2 * j + 1], ed), one, th[0][j], tl[0][j]);
+                split_pair(ldexpf(sign * dq[2 * j], ed), ldexpf(sign * dq[2 * j + 1], ed), one, th[0][j], tl[0][j], &dr[j]);
             tm_tiles<HT, KS>(act[NH - 1].h, uh);
             tm_tiles<HT, KS>(act[NH - 1].l, ul);
         }
@@ -1085,10 +1086,10 @@ __device__ __forceinline__ void train_front(const TrainArgs& a, const float* lds
                 #pragma unroll
                 for (int t = 0; t < HT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x16f16(wo[t][p], v, acc[t], 0, 0, 0);
             };
-            if (P == 3) {
-                add(P - 1, dh);
-                add(1, dl);
-            }
+            // few terms, so that an FP32 chain would have few roundings: all that the halves leave counts
+            add(0, half4{dr[0][0], dr[0][1], dr[1][0], dr[1][1]});
+            if (P == 3) add(P - 1, dh);
+            add(1, dl);
             add(1, dh);
             add(0, dl);
             add(0, dh);

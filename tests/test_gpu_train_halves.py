@@ -246,3 +246,27 @@ def test_sum_of_the_codes_gradients(nam, torch, C, hidden):
     dev = [torch.from_numpy(np.ascontiguousarray(v, np.float32)).cuda() for v in (z.numpy(), q.wi, q.wo)]
     got = model.loss_backward_codes(par, *dev, target.cuda())[1].cpu().double().sum(0)
     assert (got - total).norm() <= 2.0 ** -24 * total.norm()
+
+
+@pytest.mark.parametrize("C,hidden", [(16, [64]), (8, [32]), (16, [16])])
+def test_last_bit_of_output_gradients(nam, torch, C, hidden):
+    """Output gradients whose last bit is in neither half: each code's gradient is one product, held to
+    2^-24 in the norm over the samples (leaving the bit out would cost 2^-23 of every one)."""
+    H, n = hidden[0], 64 * 64
+    r = wl.rngs(211)
+    m = wl.make_material(r[0], r[1], 64, 64, C, 3, hidden)
+    W1, b1, W2, b2 = np.zeros((H, C + 6)), np.zeros(H), np.zeros((3, H)), np.full(3, 40.0)     # logistic(q) = 1
+    W1[:8, :8], b1[:8], W2[0, :8] = np.eye(8), 1.0, 31 / 16
+    params = np.concatenate([v.ravel() for v in (W1, b1, W2, b2)]).astype(np.float32)
+    q = wl.uniform_queries(r[2], n, 0.0, 1.0)
+    at = np.stack([np.arange(n) % 64, np.arange(n) // 64], 1)         # every sample on a texel of its own
+    q.uv[:], q.lod[:] = (at + 0.5) / 64, 0.0
+    low = (2 * r[3].integers(1024, 2047, n) + 1) * 2.0 ** -23
+    d_rgb = np.zeros((n, 3), np.float32)
+    d_rgb[:, 0] = 1.0 + r[3].integers(0, 31, n) * 2.0 ** -10 + low * r[3].choice([-1.0, 1.0], n)
+    model = nam.Model.from_workload(nam.Context(0), m)
+    tex = torch.zeros(nam.concat_levels(m.levels).shape, device="cuda")
+    dev = [torch.from_numpy(np.ascontiguousarray(v, np.float32)).cuda() for v in (q.uv, q.lod, q.wi, q.wo, d_rgb)]
+    got = model.backward(tex, torch.from_numpy(params).cuda(), *dev)[0][:n, :8].cpu().double()
+    want = torch.from_numpy(d_rgb[:, :1].astype(np.float64) * (31 / 16)).expand(n, 8)
+    assert (got - want).norm() <= 2.0 ** -24 * want.norm()

@@ -34,6 +34,9 @@ static double scale_to(double top, double x) {
 
 static bool usable_scale(double s) { return s >= std::ldexp(1.0, -100) && s <= std::ldexp(1.0, 100); }
 
+// Accumulators of this magnitude stay floats (weights far below their bias have a scale of their own).
+static bool usable_sum(double s) { return s <= std::ldexp(1.0, 120); }
+
 // FP16 of |x| < 32768, round to nearest even, and back.  (The host's _Float16 conversions are library
 // calls, most of the time of packing a decoder of three layers of 64.)
 static uint16_t half_bits(float x) {
@@ -146,7 +149,7 @@ static hipError_t pack_decode_split(nam_material* m, void* dev, std::vector<uint
         const float* b = W + (size_t)fi * fo;
         off += (size_t)fi * fo + fo;
         const auto scale_in = [&](int j) { return L > 0 ? S : j < C ? sz : sd; };
-        double wmax = 0.0, next = 0.0, step = 0.0, top_row[64] = {};
+        double wmax = 0.0, next = 0.0, step = 0.0, top_row[64] = {}, row_sum[64];
         double in_scale[64], in_bound[64], in_err[64];             // per input: 1 / scale, bound, error
         for (int j = 0; j < fi; ++j) {
             in_scale[j] = 1.0 / scale_in(j);
@@ -163,6 +166,7 @@ static hipError_t pack_decode_split(nam_material* m, void* dev, std::vector<uint
             }
             wmax = std::max(wmax, top_row[r]);
             next = std::max(next, sum);
+            row_sum[r] = sum;
             step = std::max(step, std::sqrt(sq));
         }
         err = step;
@@ -170,7 +174,7 @@ static hipError_t pack_decode_split(nam_material* m, void* dev, std::vector<uint
         double T[64];
         for (int r = 0; r < fo; ++r) {
             T[r] = scale_to(1023.0, L == NH ? top_row[r] : wmax);
-            if (!usable_scale(T[r])) return hipSuccess;
+            if (!usable_scale(T[r]) || !usable_sum(T[r] * row_sum[r])) return hipSuccess;
         }
         const int rts = L < NH ? lay.RT : 1, kss = L == 0 ? 1 : lay.KS;
         for (int j = 0; j < rts; ++j) {
@@ -227,6 +231,8 @@ static hipError_t pack_decode_split(nam_material* m, void* dev, std::vector<uint
             double sq = 0.0;
             for (int c = 0; c < C; ++c) sq += (double)W[r * C + c] * W[r * C + c];
             norm = std::max(norm, std::sqrt(sq));
+            // (no row of weights sums to more than C times its norm)
+            if (!usable_sum(up[r / 3] * sz * (std::fabs((double)W[rows_f * C + r]) + C * std::sqrt(sq) * zmax))) return hipSuccess;
             fb[r] = (float)((double)W[rows_f * C + r] * (up[r / 3] * sz));
         }
         for (int lane = 0; lane < 64; ++lane)

@@ -135,6 +135,26 @@ def test_output_biases_of_any_size(nam, ctx, torch, C, H, NH, nf, albedo, size):
     assert (np.abs(got - ref)[:, rows] <= np.where(ref[:, rows] > 1.0, 1e-6, rel) * ref[:, rows] + 2.0 ** -150).all()
 
 
+@pytest.mark.parametrize("layer,C,H,NH,nf,albedo", [("output", 16, 64, 3, 0, False), ("output", 8, 32, 2, 2, True),
+                                                    ("frames", 8, 32, 2, 2, True), ("frames", 16, 16, 1, 1, False)])
+def test_biases_far_above_their_weights(nam, ctx, torch, layer, C, H, NH, nf, albedo):
+    """Biases that the scale of tiny weights would take out of FP32."""
+    r = wl.rngs(82)
+    m = wl.make_material(r[0], r[1], 32, 32, C, 4, [H] * NH, n_frames=nf, albedo=albedo)
+    if layer == "output":
+        out = 6 if albedo else 3
+        m.params[-out * (H + 1):-out] *= np.float32(1e-22)
+        m.params[-3:] = np.float32([1e16, 1.0, 1e16])
+    else:
+        m.frame_params[:6 * nf * C] *= np.float32(1e-22)
+        m.frame_params[6 * nf * C:] = 1e16 * r[1].standard_normal(6 * nf)
+    q = wl.uniform_queries(r[2], 300, -0.5, 3.5)
+    ref = _reference(m, q, None)
+    got = nam.decode(nam.Material.from_workload(ctx, m), *nam.to_device(q)).cpu().numpy().astype(np.float64)
+    sums = _partial_sums(m, q) if layer == "frames" else 1.0
+    assert (np.abs(got - ref) <= 1e-5 * np.maximum(1.0, sums) * ref).all()
+
+
 @pytest.mark.parametrize("C,H,NH,nf", [(16, 64, 3, 2), (8, 32, 2, 1), (16, 16, 2, 2)])
 @pytest.mark.parametrize("scale", [1e-3, 1e-5, 1e-7, 1e-9])
 @pytest.mark.parametrize("everywhere", [True, False])

@@ -1444,11 +1444,11 @@ struct alignas(16) TmSmem {
 };
 
 // What bounds it: the front wave's serial chain (at 16 channels and three layers of 64, 2^20 samples of
-// given codes: 14,100 cycles per tile, of which the matrix cores are busy for 4,400; the LDS moves 50% of
+// given codes: 14,300 cycles per tile, of which the matrix cores are busy for 4,500; the LDS moves 50% of
 // what it could), and with a texture the atomics, 412 us of lines by themselves.  More waves do not fit:
 // the gradients of a back wave take 176 registers, the activations of a front wave 96, two waves per SIMD
 // have 256 each.  Measured on 2^20 samples against FP32 matrix products in the same pairs: given codes
-// 611 -> 377 us, with fetch and scatter 770 -> 474 us (scattered by the front wave 664 us); 250,007
+// 611 -> 382 us, with fetch and scatter 770 -> 476 us (scattered by the front wave 664 us); 250,007
 // samples with two frames 250 -> 162 us.
 template <int C, int H, int NH, int NF>
 __global__ void __launch_bounds__(kTMThreads, 1) train_mfma_kernel(const TrainArgs a) {
